@@ -24,8 +24,8 @@
 //   k_sort_scatter step (5): the staged movers into their holes -- or, in
 //                  pic_step, nothing: the next push fills each hole from
 //                  the staging area as it streams its section (a deferred
-//                  fill; k_fill completes one on its own when anything else
-//                  is to read the particles first).
+//                  fill; k_settle or k_fill completes one on its own when
+//                  anything else is to read the particles first).
 //
 // The cells the kernels keep are 16-bit offsets from the tile whose section
 // holds the particle (tcell_pack); the staging records carry whole-grid
@@ -738,8 +738,9 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_add_direct(SortArgs a)
     sort_add_direct_unit(a, blockIdx.y, blockIdx.x);
 }
 // A fill left pending by a deferred sort, done on its own (before anything
-// reads the particle arrays other than a push): tile t's fcount[t] staged
-// movers into its holes, as the next push would, and fcount[t] back to 0.
+// works on the tile-relative cells other than a push: the window move): tile
+// t's fcount[t] staged movers into its holes, as the next push would, and
+// fcount[t] back to 0.
 __device__ __forceinline__ void fill_unit(const SortArgs &a, int spi, int grp)
 {
     const int lane = threadIdx.x & 63;
@@ -755,29 +756,56 @@ __device__ __forceinline__ void fill_unit(const SortArgs &a, int spi, int grp)
     if (lane == 0 && m != 0) sp.fcount[t] = 0;
 }
 
-// The whole-grid cells of tile t's section into the caller's cell array
-// (one wavefront per tile), from the tile-relative ones: the cell of a
-// particle that has left its tile wraps across the periodic seam.  rebase:
-// a sorted state, each cell relative to the tile modulo its edge.
-__device__ __forceinline__ void publish_unit(const SortArgs &a, int spi, int grp, bool rebase)
+// One tile for a reader of the particle arrays, by `nt` threads of a block:
+// a fill left pending (as fill_unit), then the whole-grid cells of the tile's
+// section into the caller's cell array from the tile-relative ones (the cell
+// of a particle that has left its tile wraps across the periodic seam).
+// rebase: a sorted state, each cell relative to the tile modulo its edge.
+// All threads of the block take part (a barrier orders the fill's cells
+// before the section's reads); t may be past the last tile.
+//
+// Bound by HBM: 6 bytes a particle.  Four slots per thread and pass, from
+// 8-byte groups of the cell array on: one wavefront per tile and one slot
+// per lane, as this was first, left a 32 x 32 tile's 16,384 particles to 256
+// dependent passes.  Fill and cells, before as two launches and now: 16.8 M
+// particles in 1,024 tiles 135 -> 26 us, 67 M in 4,096 tiles 258 -> 121 us
+// (4.0 TB/s counting the staged movers), 65,536 in 16 tiles 37 -> 5 us.
+typedef int16_t vs4 __attribute__((ext_vector_type(4)));
+typedef int32_t vi4 __attribute__((ext_vector_type(4), aligned(4)));   // the caller's array: 4-byte aligned
+__device__ __forceinline__ void settle_tile(const SortArgs &a, int spi, int t, int tid, int nt, bool rebase)
 {
-    const int lane = threadIdx.x & 63;
-    const int t = grp * kSortWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (t >= a.n_tiles) return;
     const SortSpecies &sp = a.sp[spi];
+    const bool on = t < a.n_tiles;
     const int gx0 = (t % a.ntx) * a.tile, gy0 = (t / a.ntx) * a.tile;
-    const int A = sp.off[t], B = sp.off[t + 1];
+    const int A = on ? sp.off[t] : 0, B = on ? sp.off[t + 1] : 0;
+    const int m = on ? sp.fcount[t] : 0;
+    for (int k = tid; k < m; k += nt) {
+        const int64_t r = (int64_t)A + k;
+        store_parts(sp.p, sp.hole[r], load_leaver(sp.srec, r), gx0, gy0);
+    }
+    __syncthreads();
+    if (tid == 0 && m != 0) sp.fcount[t] = 0;
     const int mask = rebase ? a.tile - 1 : -1;
-    for (int i = A + lane; i < B; i += 64) {
-        const int lc = sp.p.cell[i];
-        sp.gcell[i] = wrap_s(gx0 + (tcell_x(lc) & mask), a.nx) | (wrap_s(gy0 + (tcell_y(lc) & mask), a.ny) << 16);
+    auto whole = [&](int lc) {
+        return wrap_s(gx0 + (tcell_x(lc) & mask), a.nx) | (wrap_s(gy0 + (tcell_y(lc) & mask), a.ny) << 16);
+    };
+    for (int64_t i = (int64_t)(A & ~3) + 4 * tid; i < B; i += 4 * nt) {
+        if (i >= A && i + 4 <= B) {
+            const vs4 c = *(const PIC_GLOBAL vs4 *)(sp.p.cell + i);   // the workspace's array: 256-byte aligned
+            *(PIC_GLOBAL vi4 *)(sp.gcell + i) = vi4{whole(c.x), whole(c.y), whole(c.z), whole(c.w)};
+        } else {   // the section's ends
+            for (int64_t j = i < A ? A : i; j < i + 4 && j < B; ++j) sp.gcell[j] = whole(sp.p.cell[j]);
+        }
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill(SortArgs a) { fill_unit(a, blockIdx.y, blockIdx.x); }
-__global__ void __launch_bounds__(kBlock) k_publish(SortArgs a, int rebase)
+// one tile per block of kSettleBlock threads: sixteen wavefronts, so a tile
+// of any size has its loads in flight at once also where tiles are few
+constexpr int kSettleBlock = 1024;
+__global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int rebase)
 {
-    publish_unit(a, blockIdx.y, blockIdx.x, rebase != 0);
+    settle_tile(a, blockIdx.y, blockIdx.x, threadIdx.x, kSettleBlock, rebase != 0);
 }
 template <int NB>
 __global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit<NB>(a, blockIdx.y, blockIdx.x); }
@@ -816,15 +844,12 @@ __global__ void __launch_bounds__(kBlock) k_sort_plan_b(const SortArgs *d, const
     const int4 w = it[blockIdx.x];
     sort_plan_unit<kPlanBatchB>(d[w.x], w.y, w.z);
 }
-__global__ void __launch_bounds__(kBlock) k_fill_b(const SortArgs *d, const int4 *it)
+// the kSortWaves tiles of an item side by side, a quarter of the block each
+__global__ void __launch_bounds__(kSettleBlock) k_settle_b(const SortArgs *d, const int4 *it, int rebase)
 {
+    constexpr int nt = kSettleBlock / kSortWaves;
     const int4 w = it[blockIdx.x];
-    fill_unit(d[w.x], w.y, w.z);
-}
-__global__ void __launch_bounds__(kBlock) k_publish_b(const SortArgs *d, const int4 *it, int rebase)
-{
-    const int4 w = it[blockIdx.x];
-    publish_unit(d[w.x], w.y, w.z, rebase != 0);
+    settle_tile(d[w.x], w.y, w.z * kSortWaves + threadIdx.x / nt, threadIdx.x % nt, nt, rebase != 0);
 }
 
 __global__ void __launch_bounds__(kBlock) k_motion_scatter_b(const SortArgs *d, const int4 *it)
@@ -914,21 +939,16 @@ void launch_fill(const SortArgs &a, int n_tiles, hipStream_t s)
     hipLaunchKernelGGL(k_fill, dim3((n_tiles + kSortWaves - 1) / kSortWaves, a.n_species), dim3(kBlock), 0, s, a);
 }
 
-void launch_fill_batch(const SortBatch &b, hipStream_t s)
+void launch_settle(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s)
 {
-    if (b.n_plan > 0) hipLaunchKernelGGL(k_fill_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
+    hipLaunchKernelGGL(k_settle, dim3(n_tiles, a.n_species), dim3(kSettleBlock), 0, s, a, rebase ? 1 : 0);
 }
 
-void launch_publish(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_publish, dim3((n_tiles + kSortWaves - 1) / kSortWaves, a.n_species), dim3(kBlock), 0, s, a,
-                       rebase ? 1 : 0);
-}
-
-void launch_publish_batch(const SortBatch &b, bool rebase, hipStream_t s)
+void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s)
 {
     if (b.n_plan > 0)
-        hipLaunchKernelGGL(k_publish_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items, rebase ? 1 : 0);
+        hipLaunchKernelGGL(k_settle_b, dim3(b.n_plan), dim3(kSettleBlock), 0, s, b.descs, b.plan_items,
+                           rebase ? 1 : 0);
 }
 
 void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s)

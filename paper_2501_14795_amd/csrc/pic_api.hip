@@ -918,8 +918,8 @@ static int settle(pic_sim *S, hipStream_t stream, bool publish = true)
 {
     const SortArgs a = sort_args(S);
     if (motion_deferrable(S)) launch_motion_copy_live(a, S->n_tiles, stream);   // a copy back left pending
-    launch_fill(a, S->n_tiles, stream);
-    if (publish) launch_publish(a, S->n_tiles, S->since_sort == 0, stream);
+    if (publish) launch_settle(a, S->n_tiles, S->since_sort == 0, stream);
+    else launch_fill(a, S->n_tiles, stream);
     return hip_ok(hipGetLastError());
 }
 
@@ -1611,8 +1611,7 @@ int pic_batch_sync(pic_batch *B, hipStream_t stream)
     sb.plan_items = B->plan_items;
     sb.n_plan = B->n_plan;
     sb.max_blocks = B->max_blocks;
-    launch_fill_batch(sb, stream);   // members without a pending fill have zero fill counts
-    launch_publish_batch(sb, B->phase == 0, stream);
+    launch_settle_batch(sb, B->phase == 0, stream);   // members without a pending fill have zero fill counts
     return hip_ok(hipGetLastError());
 }
 

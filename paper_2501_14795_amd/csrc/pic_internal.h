@@ -84,9 +84,9 @@ void launch_sort_scan(const SortArgs &a, int n_tiles, hipStream_t s);
 void launch_sort_plan(const SortArgs &a, int n_tiles, hipStream_t s);
 void launch_sort_scatter(const SortArgs &a, int n_tiles, hipStream_t s);
 void launch_fill(const SortArgs &a, int n_tiles, hipStream_t s);
-// the whole-grid cells of every particle into the caller's cell arrays
-// (gcell); rebase: no push since the last sort
-void launch_publish(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s);
+// a pending hole fill, and the whole-grid cells of every particle into the
+// caller's cell arrays (gcell); rebase: no push since the last sort
+void launch_settle(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s);
 // tile-relative cells of n particles grouped by tile, inside their tiles
 void launch_localize(const int32_t *cell, int16_t *lcell, int32_t n, int tile, hipStream_t s);
 
@@ -100,9 +100,8 @@ struct SortBatch {
     const int4 *plan_items; int n_plan;
     int max_blocks;   // the most scan blocks of one member
 };
-// a pending hole fill of every member (fill_unit), and the publish of their cells
-void launch_fill_batch(const SortBatch &b, hipStream_t s);
-void launch_publish_batch(const SortBatch &b, bool rebase, hipStream_t s);
+// launch_settle for every member
+void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s);
 // motion: the motion-class sort (PIC_FLAG_MOTION_SORT) instead of the in-place one
 void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s);
 // the motion-class sort after the recount and scan: every particle into the
