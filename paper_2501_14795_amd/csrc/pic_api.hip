@@ -112,7 +112,7 @@ Layout make_layout(const pic_config *c)
     };
     L.err = take(64);
     L.stg_live = take(64);
-    L.dacc = take(32 * sizeof(double));
+    L.dacc = take(kDiagSlots * kDiagStride * sizeof(double));
     L.cacc = take(8 * sizeof(unsigned long long));
     const int NJ = T + 2 * halo_of(c) + 1;   // current halo nodes per axis
     L.jtile = take((size_t)n_tiles * 3 * NJ * NJ * sizeof(float));
@@ -324,13 +324,14 @@ DiagSpecies diag_species(const pic_sim *s, int k)
 {
     DiagSpecies d;
     const pic_particles &p = s->buf.sp[k];
-    d.cell = p.cell;
-    d.x = p.x;
-    d.y = p.y;
-    d.ux = p.ux;
-    d.uy = p.uy;
-    d.uz = p.uz;
+    d.p = Parts{s->sp[k].lcell, p.x, p.y, p.ux, p.uy, p.uz};
+    d.off = s->sp[k].off;
     d.n = (int32_t)s->cfg.species[k].n;
+    d.nx = s->cfg.nx;
+    d.ny = s->cfg.ny;
+    d.ntx = s->ntx;
+    d.tile = s->tile;
+    d.mask = s->since_sort == 0 ? s->tile - 1 : -1;
     d.q = s->cfg.species[k].q;
     d.quadratic = d_mode(&s->cfg) == kDepQuad ? 1 : 0;
     return d;
@@ -339,13 +340,15 @@ DiagSpecies diag_species(const pic_sim *s, int k)
 // The node charge density of the Gauss diagnostic into rho_now: every
 // species' charge at the nodes, binomially filtered like the current when the
 // filter is on (the density whose continuity the filtered current satisfies).
-int node_density(pic_sim *S, hipStream_t stream)
+// acc (unless null): the diagnostics' accumulators are cleared too, and with
+// `kinetic` the same pass over the particles sums their kinetic energies.
+int node_density(pic_sim *S, hipStream_t stream, double *acc = nullptr, bool kinetic = false)
 {
     const pic_config &c = S->cfg;
     const int64_t plane = (int64_t)c.nx * c.ny;
-    int rc = hip_ok(hipMemsetAsync(S->rho_now, 0, plane * sizeof(double), stream));
-    if (rc) return rc;
-    for (int s = 0; s < c.n_species; ++s) launch_diag_rho(diag_species(S, s), c.nx, c.ny, S->rho_now, stream);
+    launch_diag_clear(acc, S->rho_now, plane, stream);
+    for (int s = 0; s < c.n_species; ++s)
+        launch_diag_particles(diag_species(S, s), S->n_tiles, S->rho_now, acc, kinetic ? kDiagUk + s : 0, stream);
     for (int p = 0; p < c.j_filter; ++p) {
         FilterArgs f;
         f.src = (p & 1) ? S->rho_tmp : S->rho_now;
@@ -356,8 +359,8 @@ int node_density(pic_sim *S, hipStream_t stream)
         launch_filter(f, true, stream);
     }
     if (c.j_filter & 1)
-        rc = hip_ok(hipMemcpyAsync(S->rho_now, S->rho_tmp, plane * sizeof(double), hipMemcpyDeviceToDevice, stream));
-    return rc;
+        return hip_ok(hipMemcpyAsync(S->rho_now, S->rho_tmp, plane * sizeof(double), hipMemcpyDeviceToDevice, stream));
+    return hip_ok(hipGetLastError());
 }
 
 // The uniform neutralising background: the mean charge density.
@@ -1105,25 +1108,33 @@ int pic_diag(pic_sim *S, unsigned what, pic_diag_out *out, hipStream_t stream)
     const int64_t plane = (int64_t)c.nx * c.ny;
     if ((what & PIC_DIAG_CONTINUITY) && !S->have_snapshot) return PIC_EINVAL;
     int rc = settle(S, stream);
-    if (rc == PIC_OK) rc = hip_ok(hipMemsetAsync(S->dacc, 0, 32 * sizeof(double), stream));
-    if (rc == PIC_OK) rc = hip_ok(hipMemsetAsync(S->cacc, 0, 8 * sizeof(unsigned long long), stream));
     if (rc) return rc;
-    if (what & PIC_DIAG_ENERGY) {
-        launch_diag_field_energy(S->buf.fields, plane, S->dacc, stream);
-        for (int s = 0; s < c.n_species; ++s) launch_diag_kinetic(diag_species(S, s), S->dacc + 2 + s, stream);
-    }
     if (what & (PIC_DIAG_RHO_SNAPSHOT | PIC_DIAG_CONTINUITY | PIC_DIAG_GAUSS)) {
-        rc = node_density(S, stream);
+        rc = node_density(S, stream, S->dacc, (what & PIC_DIAG_ENERGY) != 0);
         if (rc) return rc;
+    } else {
+        launch_diag_clear(S->dacc, nullptr, 0, stream);
+        if (what & PIC_DIAG_ENERGY)
+            for (int s = 0; s < c.n_species; ++s)
+                launch_diag_particles(diag_species(S, s), S->n_tiles, nullptr, S->dacc, kDiagUk + s, stream);
     }
-    if (what & PIC_DIAG_CONTINUITY)
-        launch_diag_continuity(S->rho_prev, S->rho_now, S->buf.fields + 6 * plane, c.nx, c.ny, c.dt, c.dx, c.dy,
-                               S->dacc + 8, stream);
-    if (what & PIC_DIAG_GAUSS)
-        launch_diag_gauss(S->buf.fields, S->rho_now, mean_density(S), c.nx, c.ny, c.dx, c.dy, S->dacc + 10, stream);
-    double dh[32];
+    if (what & (PIC_DIAG_ENERGY | PIC_DIAG_CONTINUITY | PIC_DIAG_GAUSS)) {
+        DiagGrid g;
+        g.fld = S->buf.fields;
+        g.rho = S->rho_now;
+        g.rho_prev = S->rho_prev;
+        g.rho_bar = mean_density(S);
+        g.nx = c.nx;
+        g.ny = c.ny;
+        g.dt = c.dt;
+        g.dx = c.dx;
+        g.dy = c.dy;
+        g.acc = S->dacc;
+        launch_diag_grid(g, what, stream);
+    }
+    double acc[kDiagSlots * kDiagStride];
     unsigned long long ch[8 * kMaxSpecies];
-    rc = hip_ok(hipMemcpyAsync(dh, S->dacc, sizeof(dh), hipMemcpyDeviceToHost, stream));
+    rc = hip_ok(hipMemcpyAsync(acc, S->dacc, sizeof(acc), hipMemcpyDeviceToHost, stream));
     if (rc == PIC_OK && (what & PIC_DIAG_COUNTS)) {
         for (int s = 0; s < c.n_species && rc == PIC_OK; ++s) {
             rc = hip_ok(hipMemsetAsync(S->cacc, 0, 2 * sizeof(unsigned long long), stream));
@@ -1136,20 +1147,27 @@ int pic_diag(pic_sim *S, unsigned what, pic_diag_out *out, hipStream_t stream)
     }
     if (rc == PIC_OK) rc = hip_ok(hipStreamSynchronize(stream));
     if (rc) return rc;
+    double dh[kDiagStride] = {};
+    for (int b = 0; b < kDiagSlots; ++b)
+        for (int k = 0; k < kDiagStride; ++k) {
+            const double v = acc[b * kDiagStride + k];
+            if (k < kDiagCont) dh[k] += v;
+            else if (dh[k] == dh[k] && !(v <= dh[k])) dh[k] = v;   // maxima; a NaN, once met, stays
+        }
     if (what & PIC_DIAG_ENERGY) {
         const double dA = c.dx * c.dy;
-        out->u_e = 0.5 * dA * dh[0];
-        out->u_b = 0.5 * dA * dh[1];
+        out->u_e = 0.5 * dA * dh[kDiagUe];
+        out->u_b = 0.5 * dA * dh[kDiagUb];
         for (int s = 0; s < c.n_species; ++s)
-            out->u_k[s] = dA * (c.species[s].q / c.species[s].qm) * dh[2 + s];
+            out->u_k[s] = dA * (c.species[s].q / c.species[s].qm) * dh[kDiagUk + s];
     }
     if (what & PIC_DIAG_CONTINUITY) {
-        out->continuity_max = dh[8];
-        out->rho_max = dh[9];
+        out->continuity_max = dh[kDiagCont];
+        out->rho_max = dh[kDiagRhoMax];
     }
     if (what & PIC_DIAG_GAUSS) {
-        out->gauss_max = dh[10];
-        out->divb_max = dh[11];
+        out->gauss_max = dh[kDiagGauss];
+        out->divb_max = dh[kDiagDivb];
     }
     if (what & PIC_DIAG_COUNTS)
         for (int s = 0; s < c.n_species; ++s) {

@@ -175,21 +175,38 @@ struct CgResult {
 CgResult cg_project(float *fld, const double *rho, double rho_bar, int magnetic, int nx, int ny, double dx, double dy,
                     double tol, int max_iter, const CgScratch &w, hipStream_t s);
 
+// The diagnostics' accumulators: kDiagSlots sets of kDiagStride doubles (a
+// block adds to one of them; the host folds them).
+constexpr int kDiagSlots = 64;
+constexpr int kDiagStride = 16;
+enum : int { kDiagUe = 0, kDiagUb = 1, kDiagUk = 2, kDiagCont = 8, kDiagRhoMax = 9, kDiagGauss = 10, kDiagDivb = 11 };
+static_assert(kDiagUk + kMaxSpecies <= kDiagCont && kDiagDivb < kDiagStride, "diagnostic accumulator set");
+
 struct DiagSpecies {
-    const int32_t *cell;
-    const float *x, *y, *ux, *uy, *uz;
+    Parts p;         // tile-relative cells
+    const int32_t *off;
     int32_t n;
+    int nx, ny, ntx, tile;
+    int n_tiles, range;   // set by the launcher: slots per block
+    int mask;        // tile - 1 in a sorted state (cells relative to their tile modulo its edge), else -1
     double q;
     int quadratic;   // the particle shape: 0 linear, 1 quadratic B-spline
 };
-void launch_diag_field_energy(const float *fld, int64_t plane, double *acc, hipStream_t s);
-void launch_diag_kinetic(const DiagSpecies &sp, double *acc, hipStream_t s);
-void launch_diag_rho(const DiagSpecies &sp, int nx, int ny, double *rho, hipStream_t s);
-void launch_diag_continuity(const double *rho_prev, const double *rho_now, const float *J,
-                            int nx, int ny, double dt, double dx, double dy, double *acc,
-                            hipStream_t s);
-void launch_diag_gauss(const float *fld, const double *rho, double rho_bar, int nx, int ny, double dx, double dy,
-                       double *acc, hipStream_t s);
+struct DiagGrid {
+    const float *fld;
+    const double *rho, *rho_prev;
+    double rho_bar;
+    int nx, ny;
+    double dt, dx, dy;
+    double *acc;
+};
+// acc (the accumulators) and rho (plane values), each unless null, to zero
+void launch_diag_clear(double *acc, double *rho, int64_t plane, hipStream_t s);
+// rho (unless null) += the species' charge at the nodes; entry kin (unless 0)
+// of the accumulators += its sum of gamma - 1
+void launch_diag_particles(const DiagSpecies &sp, int n_tiles, double *rho, double *acc, int kin, hipStream_t s);
+// what: PIC_DIAG_ENERGY, PIC_DIAG_CONTINUITY and PIC_DIAG_GAUSS
+void launch_diag_grid(const DiagGrid &g, unsigned what, hipStream_t s);
 void launch_diag_counts(const int32_t *cnt, const int32_t *mcount, int n_tiles,
                         unsigned long long *acc, hipStream_t s);
 
