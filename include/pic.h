@@ -374,9 +374,11 @@ int pic_diag(pic_sim *sim, unsigned what, pic_diag_out *out, hipStream_t stream)
  * Ez, Bz are not touched.  From E = B = 0 this is the electrostatic field of
  * the particles (e.g. a perturbed plasma).  rho is that of the Gauss
  * diagnostic (binomially filtered when pic_config.j_filter > 0).  Each
- * Poisson problem is solved by conjugate gradients in FP64 until ||r|| <= tol
- * ||r0|| (tol <= 0: 1e-12) or max_iter iterations (<= 0: 20 max(nx, ny) +
- * 100); the result is stored in FP32.
+ * Poisson problem is solved in FP64 until ||r|| <= tol ||r0|| (tol <= 0:
+ * 1e-12); the result is stored in FP32.  max_iter <= 0: directly, by Hartley
+ * transforms, and again on the residual while that is above tol (each such
+ * solve counts as one iteration; at most 20 max(nx, ny) + 100).  max_iter > 0:
+ * by at most max_iter iterations of conjugate gradients.
  * scratch: device memory of at least PIC_GAUSS_SCRATCH_BYTES(nx, ny) bytes,
  * 256-byte aligned, caller-owned.  Synchronises `stream`.  out (may be NULL)
  * receives the iterations and final relative residual of both solves.

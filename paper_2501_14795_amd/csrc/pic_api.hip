@@ -380,7 +380,10 @@ int solve_gauss_in(pic_sim *S, double *d, double tol, int max_iter, pic_gauss_ou
     const pic_config &c = S->cfg;
     const int64_t P = (int64_t)c.nx * c.ny;
     if (!(tol > 0.0)) tol = 1e-12;
-    if (max_iter <= 0) max_iter = 20 * (c.nx > c.ny ? c.nx : c.ny) + 100;
+    // a caller's cap counts iterations of conjugate gradients; without one the
+    // direct solve, far faster at every size
+    const bool direct = max_iter <= 0;
+    if (direct) max_iter = 20 * (c.nx > c.ny ? c.nx : c.ny) + 100;
     CgScratch w;
     w.x = d;
     w.r = d + P;
@@ -388,12 +391,15 @@ int solve_gauss_in(pic_sim *S, double *d, double tol, int max_iter, pic_gauss_ou
     w.q = d + 3 * P;
     w.partial = d + 4 * P;
     w.scal = w.partial + kCgPartials;
+    w.tab = S->rho_prev;   // the snapshot is dropped by a solve
+    S->have_snapshot = false;
     int rc = node_density(S, stream);
     if (rc) return rc;
     const CgResult e = cg_project(S->buf.fields, S->rho_now, mean_density(S), 0, c.nx, c.ny, c.dx, c.dy, tol,
-                                  max_iter, w, stream);
+                                  max_iter, direct, w, stream);
     if (e.iterations < 0) return PIC_EHIP;
-    const CgResult b = cg_project(S->buf.fields, nullptr, 0.0, 1, c.nx, c.ny, c.dx, c.dy, tol, max_iter, w, stream);
+    const CgResult b = cg_project(S->buf.fields, nullptr, 0.0, 1, c.nx, c.ny, c.dx, c.dy, tol, max_iter, direct, w,
+                                  stream);
     if (b.iterations < 0) return PIC_EHIP;
     rc = hip_ok(hipGetLastError());
     if (rc == PIC_OK) rc = hip_ok(hipStreamSynchronize(stream));
@@ -404,7 +410,6 @@ int solve_gauss_in(pic_sim *S, double *d, double tol, int max_iter, pic_gauss_ou
         out->residual[0] = e.residual;
         out->residual[1] = b.residual;
     }
-    S->have_snapshot = false;
     return e.converged && b.converged ? PIC_OK : PIC_ENOCONV;
 }
 

@@ -160,12 +160,14 @@ void launch_field_advance(const FieldArgs &f, int tile, int halo, hipStream_t s)
 void launch_field_advance_batch(const FieldArgs *descs, const int4 *items, int n_items, bool fold, bool bh, int tile,
                                 int halo, hipStream_t s);
 
-// Conjugate-gradient projection of E (Eq. 17) or B (Eq. 18), k_poisson.hip.
+// Projection of E (Eq. 17) or B (Eq. 18) by a direct solve or by conjugate
+// gradients, k_poisson.hip.
 constexpr int kCgPartials = 1024;   // per-block partial sums of one dot product, at most
 struct CgScratch {
     double *x, *r, *p, *q;   // nx * ny each
     double *partial;         // kCgPartials
     double *scal;            // r.r (two parity slots), p.q, sum of the right-hand side
+    double *tab;             // the direct solve's tables, 2 (nx + ny) (at most nx * ny: both are at least 8)
 };
 struct CgResult {
     int iterations;   // -1: a HIP call failed
@@ -173,7 +175,7 @@ struct CgResult {
     bool converged;
 };
 CgResult cg_project(float *fld, const double *rho, double rho_bar, int magnetic, int nx, int ny, double dx, double dy,
-                    double tol, int max_iter, const CgScratch &w, hipStream_t s);
+                    double tol, int max_iter, bool direct, const CgScratch &w, hipStream_t s);
 
 // The diagnostics' accumulators: kDiagSlots sets of kDiagStride doubles (a
 // block adds to one of them; the host folds them).
