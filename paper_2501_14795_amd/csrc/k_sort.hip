@@ -2,11 +2,12 @@
 // redesigned for gfx950: no atomics decide any position, so the permutation
 // is the canonical one and is reproducible bit for bit.
 //
-//   k_sort_count, k_sort_add_direct (k_sort_scan_blocks, k_sort_add_base
-//                  above 64 scan blocks)
+//   k_sort_count (and k_sort_scan_blocks above 64 scan blocks)
 //                  step (1): the new count of tile t is the sum, over the nine
 //                  tiles a particle can come from, of the direction counts the
-//                  push kernel recorded; an exclusive scan gives tile_offset'.
+//                  push kernel recorded, with its prefix in a block of 256
+//                  tiles; k_sort_plan adds the blocks before its own and writes
+//                  tile_offset'.  Up to 256 tiles the plan counts by itself.
 //   k_sort_plan    steps (2)-(4), one wavefront per destination tile t with
 //                  new section [A, B):
 //                    holes  = slots of [A, B) whose particle is not in tile t,
@@ -15,8 +16,9 @@
 //                             own leavers inside it (from its leaver lists);
 //                    movers = particles of tile t outside [A, B), ascending:
 //                             the leavers of the up-to-eight neighbour tiles
-//                             heading to t (their leaver lists) and t's own
-//                             stayers pushed out of [A, B) by section shifts;
+//                             heading to t (the push lists them by direction)
+//                             and t's own stayers pushed out of [A, B) by
+//                             section shifts;
 //                  every mover is copied, in hole order, to a staging area
 //                  (contiguous stores), so only O(movers) particle bytes
 //                  are touched and no particle slot is written while other
@@ -87,17 +89,10 @@ __device__ __forceinline__ int tile_count_in(const int32_t *cnt, int t, int ntx,
     return v;
 }
 
-// Step (1), first pass: new count of every tile and its exclusive prefix
-// within its block of kScanBlock tiles, in place of tile_offset (which goes
-// to offp, the plan's old sections); block totals to bsum.
-__device__ __forceinline__ void sort_count_unit(const SortArgs &a, int spi, int blk)
+// Exclusive scan of one int per thread over a block of kScanBlock threads;
+// returns the thread's prefix and the block total.  All threads take part.
+__device__ __forceinline__ int block_exclusive(int c, int &total)
 {
-    const SortSpecies &sp = a.sp[spi];
-    const int n_tiles = a.n_tiles;
-    const int t = blk * kScanBlock + threadIdx.x;
-    int c = t < n_tiles ? tile_count_in(sp.cnt, t, a.ntx, a.nty) : 0;
-    if (t < n_tiles && sp.inj_off) c += sp.inj_off[t + 1] - sp.inj_off[t];   // the window's new particles
-    // block exclusive scan (kScanBlock = 256: four wavefronts)
     __shared__ int s_w[kScanBlock / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int x = c;
@@ -109,13 +104,45 @@ __device__ __forceinline__ void sort_count_unit(const SortArgs &a, int spi, int 
     if (lane == 63) s_w[w] = x;
     __syncthreads();
     int base = 0;
-    for (int k = 0; k < w; ++k) base += s_w[k];
-    if (t < n_tiles) {
-        sp.offp[t] = sp.off[t];
-        sp.off[t] = base + x - c;
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < kScanBlock / 64; ++k) {
+        if (k < w) base += s_w[k];
+        total += s_w[k];
     }
-    if (t == n_tiles - 1) sp.offp[n_tiles] = sp.off[n_tiles];
-    if (threadIdx.x == kScanBlock - 1) sp.bsum[blk] = base + x;
+    return base + x - c;
+}
+
+// The new count of tile t: what the push recorded, and the window's new
+// particles (0 past the last tile).
+__device__ __forceinline__ int tile_count_new(const SortArgs &a, const SortSpecies &sp, int t)
+{
+    if (t >= a.n_tiles) return 0;
+    int c = tile_count_in(sp.cnt, t, a.ntx, a.nty);
+    if (sp.inj_off) c += sp.inj_off[t + 1] - sp.inj_off[t];
+    return c;
+}
+
+// What the new counts must add up to.
+__device__ __forceinline__ int sort_expect(const SortSpecies &sp)
+{
+    return sp.removed ? sp.n - *sp.removed + sp.inj_n : sp.n;
+}
+
+// Step (1), first pass: new count of every tile and its exclusive prefix
+// within its block of kScanBlock tiles; block totals to bsum.
+__device__ __forceinline__ void sort_count_unit(const SortArgs &a, int spi, int blk)
+{
+    const SortSpecies &sp = a.sp[spi];
+    const int t = blk * kScanBlock + threadIdx.x;
+    const int c = tile_count_new(a, sp, t);
+    int total;
+    const int ex = block_exclusive(c, total);
+    if (t < a.n_tiles) {
+        sp.pre[t] = ex;
+        sp.cnew[t] = c;
+    }
+    if (threadIdx.x == 0) sp.bsum[blk] = total;
 }
 
 // Step (1), second pass (one block per species): exclusive scan of the block
@@ -137,17 +164,17 @@ __device__ __forceinline__ void sort_scan_unit(const SortArgs &a, int spi)
     }
     if (threadIdx.x == 0) {
         sp.off[n_tiles] = carry;
-        const int expect = sp.removed ? sp.n - *sp.removed + sp.inj_n : sp.n;
-        if (carry != expect) atomicOr(a.err, kErrCount);
+        if (carry != sort_expect(sp)) atomicOr(a.err, kErrCount);
     }
 }
 
-// Step (1), third pass: add each block's base.
+// Step (1), third pass where no plan follows (the motion-class sort): add
+// each block's base.
 __device__ __forceinline__ void sort_add_unit(const SortArgs &a, int spi, int blk)
 {
     const SortSpecies &sp = a.sp[spi];
     const int t = blk * kScanBlock + threadIdx.x;
-    if (t < a.n_tiles) sp.off[t] += sp.bsum[blk];
+    if (t < a.n_tiles) sp.off[t] = sp.pre[t] + sp.bsum[blk];
 }
 
 // Step (1), second and third pass in one, while there are at most
@@ -171,26 +198,23 @@ __device__ __forceinline__ void sort_add_direct_unit(const SortArgs &a, int spi,
 #pragma unroll
     for (int k = 0; k < kScanBlock / 64; ++k) base += s_w[k];
     const int t = blk * kScanBlock + threadIdx.x;
-    if (t < n_tiles) sp.off[t] += base;
+    if (t < n_tiles) sp.off[t] = sp.pre[t] + base;
     if (blk == nb - 1 && threadIdx.x == 0) {
         const int total = base + sp.bsum[blk];
         sp.off[n_tiles] = total;
-        const int expect = sp.removed ? sp.n - *sp.removed + sp.inj_n : sp.n;
-        if (total != expect) atomicOr(a.err, kErrCount);
+        if (total != sort_expect(sp)) atomicOr(a.err, kErrCount);
     }
 }
 
 // Slot of the list holding flat index k, over the lists described by lanes
-// 0..63 (exclusive prefix `ex` of their lengths, INT_MAX past the last list):
-// the largest L with ex_L <= k.  Fixed-step binary search, all lanes active.
+// 0..31 (exclusive prefix `ex` of their lengths): the largest L with ex_L <=
+// k.  Fixed-step binary search, all lanes active.
 __device__ __forceinline__ int find_list(int k, int ex)
 {
     int lo = 0;
 #pragma unroll
-    for (int step = 32; step > 0; step >>= 1) {
-        const int e = __shfl(ex, lo + step < 64 ? lo + step : 63, 64);
-        if (lo + step < 64 && e <= k) lo += step;
-    }
+    for (int step = 16; step > 0; step >>= 1)
+        if (__shfl(ex, lo + step, 64) <= k) lo += step;
     return lo;
 }
 
@@ -252,36 +276,42 @@ __device__ __forceinline__ bool tcell_inside(int lc, int T)
 }
 
 // Steps (2)-(4) of the sort for one destination tile t per wavefront, new
-// section [A, B), old section [oA, oB).  Every candidate list of holes and
-// of movers is described by one list slot (two per lane: slots lane and
-// lane + 64); the lists are streamed as one flat index space, holes first,
-// and compacted with ballots, which keeps both outputs in ascending slot
-// order.  W = leaver sub-lists per tile (the push kernel's wavefronts per
-// tile).  List slots:
+// section [A, B), old section [oA, oB).  Every candidate list of holes and of
+// movers is described by one lane; the lists are streamed as one flat index
+// space, holes first, and compacted with ballots, which keeps both outputs in
+// ascending slot order.  W = leaver sub-lists per tile (the push kernel's
+// wavefronts per tile).  Lists:
 //   0             : holes in [A, min(B, oA)), slots of lower old sections
 //                   (hole unless the particle there moved into t)
 //   1 .. W        : holes among t's W leaver sub-lists, restricted to
 //                   [max(A, oA), min(B, oB))
 //   W + 1         : holes in [max(A, oB), B), slots of higher old sections
-//   W + 2 + q W + w : movers from the source tile of rank q (the nine tiles a
-//                   particle of t can come from, ascending, duplicates
-//                   dropped): s != t -- s's leaver sub-list w, entries heading
-//                   to t whose slot is outside [A, B), data from the leaver
-//                   records; s == t -- (w = 0, 1) t's slots outside [A, B)
-//                   whose particle kept tile t
-//   W + 2 + 9 W, +1 : the moving window's new particles for t outside [A, B)
+//   W + 2 .. W + 11 : movers by source tile, ascending: of each of the eight
+//                   neighbours the leavers heading to t (the push lists a
+//                   tile's leavers by direction, each direction in slot
+//                   order) whose slot is outside [A, B), data from the leaver
+//                   records; at t's own place two lists, t's slots below A
+//                   and from B on whose particle kept tile t
+//   W + 12, + 13  : the moving window's new particles for t outside [A, B)
 // The loads are staged so that each round trip to memory serves all lists at
-// once: the list bounds, then the candidates (kPlanBatch iterations of 64),
-// then the movers' data, then the stores.
-// candidate iterations per round trip: 6 while every tile's wavefront is
+// once: the list bounds, then the candidates (NB iterations of 64), then the
+// movers' data, then the stores.
+//
+// Bound by that chain of round trips and by the lane exchanges of the list
+// search.  Reading a neighbour's leavers for one direction instead of all of
+// them cuts the candidates to about a fourth and the lists to half a
+// wavefront's lanes: 4,096 32 x 32 tiles (253 K movers) 75 -> 30 us beside the
+// field half, 2,048 16 x 16 ones (512^2, two beams) 46 -> 26, 64 batched
+// simulations 86 -> 43.
+//
+// NB, candidate iterations per round trip: 6 while every tile's wavefront is
 // resident at once (2048^2 in 32 x 32 tiles: each wavefront's chain of round
 // trips is what counts); 2 for more tiles (a batch's tens of thousands, or
 // small tiles of one large grid), which take several rounds of resident
 // wavefronts, so fewer registers (more wavefronts per SIMD) count more
 constexpr int kPlanBatch = 6;
 constexpr int kPlanBatchB = 2;
-enum : int { kListHoleRange = 0, kListHoleLeav = 1, kListMoverRange = 2, kListMoverLeav = 3 };
-static_assert(10 * push_waves(32) + 4 <= 128 && 10 * push_waves(8) + 4 <= 128, "sort plan list slots");
+static_assert(kMaxWaves + 14 <= 32, "sort plan lists");
 
 template <int NB = kPlanBatch>
 __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int grp)
@@ -290,29 +320,92 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
     // one tile per wavefront: the index is wavefront-uniform (scalar registers)
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = grp * kSortWaves + wv;
-    if (t >= a.n_tiles) return;   // whole wavefront
     const SortSpecies &sp = a.sp[spi];
+    const int n_tiles = a.n_tiles;
+
+    // ---------------- the new section
+    int A, B;
+    if (a.scan == kScanLocal) {
+        // every block counts all (at most kScanBlock) tiles by itself
+        __shared__ int s_off[kScanBlock + 1];
+        int total;
+        const int ex = block_exclusive(tile_count_new(a, sp, threadIdx.x), total);
+        s_off[threadIdx.x] = ex;
+        if (threadIdx.x == 0) s_off[kScanBlock] = total;
+        __syncthreads();
+        if (t >= n_tiles) return;   // whole wavefront
+        A = s_off[t];
+        B = s_off[t + 1];
+    } else {
+        if (t >= n_tiles) return;
+        const int blk = t / kScanBlock;
+        int base;
+        if (a.scan == kScanSums) {   // bsum: block totals, at most kScanDirect of them
+            base = lane < blk ? sp.bsum[lane] : 0;
+            A = sp.pre[t];
+            B = sp.cnew[t];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
+        } else {                     // bsum: their exclusive prefix
+            base = sp.bsum[blk];
+            A = sp.pre[t];
+            B = sp.cnew[t];
+        }
+        A += base;
+        B += A;
+    }
+    if (lane == 0) {
+        sp.off[t] = A;
+        if (t == n_tiles - 1) {
+            sp.off[n_tiles] = B;
+            if (B != sort_expect(sp)) atomicOr(a.err, kErrCount);
+        }
+    }
+
     const int ntx = a.ntx, nty = a.nty;
     const int T = a.tile;
-    const int W = push_waves(T);   // leaver sub-lists per tile
+    const int W = a.waves;   // leaver sub-lists per tile
     const int tx = t % ntx, ty = t / ntx;
     const int gx0 = tx * T, gy0 = ty * T;
 
-    // ---------------- the sources of t and their ranks (lanes 0..8)
-    int so = -1;
-    if (lane < 9) so = wrap_s(ty - (lane / 3 - 1), nty) * ntx + wrap_s(tx - (lane % 3 - 1), ntx);
-    int rank = 0, first = 1;
+    // ---------------- the sources of t (lane o < 9: the tile from which
+    // direction o leads to t), their old sections and their lists for t
+    int so = -1, so_a = 0, so_b = 0, lbase = 0, llen = 0;
+    bool bad = false;
+    if (lane < 9) {
+        so = wrap_s(ty - (lane / 3 - 1), nty) * ntx + wrap_s(tx - (lane % 3 - 1), ntx);
+        const PIC_GLOBAL vi4a *rec = (const PIC_GLOBAL vi4a *)(sp.cnt + (int64_t)so * kCntStride);
+        const vi4a r0 = rec[0], r1 = rec[1];
+        const int r8 = gp(sp.cnt)[(int64_t)so * kCntStride + 8];
+        so_a = gp(sp.offp)[so];
+        so_b = gp(sp.offp)[so + 1];
+        const int c[9] = {r0.x, r0.y, r0.z, r0.w, 0, r1.y, r1.z, r1.w, r8};   // direction 4 has no list
+        int start = 0;
+#pragma unroll
+        for (int d = 0; d < 9; ++d) {
+            if (d < lane) start += c[d];
+            if (d == lane) llen = c[d];
+        }
+        bad = start < 0 || llen < 0 || start + llen > so_b - so_a;
+        if (bad) start = llen = 0;
+        lbase = so_a + start;
+    }
+    const int sub = lane >= 1 && lane <= W ? gp(sp.cnt)[(int64_t)t * kCntStride + kCntSub + lane - 1] : 0;
+    int i0 = 0, i1 = 0;
+    if (sp.inj_off) {
+        i0 = sp.n + sp.inj_off[t];
+        i1 = sp.n + sp.inj_off[t + 1];
+    }
+    // the order of the sources: by tile (equal ones, on an axis of one or two
+    // tiles, by direction: all but one of their lists are empty)
+    int rank = 0;
 #pragma unroll
     for (int o = 0; o < 9; ++o) {
-        const int v = __shfl(so, o, 64);
-        bool vfirst = true;
-        for (int o2 = 0; o2 < o; ++o2)
-            if (__shfl(so, o2, 64) == v) vfirst = false;
-        if (vfirst && v < so) ++rank;
-        if (o < lane && v == so) first = 0;
+        const int v = __builtin_amdgcn_readlane(so, o);
+        if (v < so || (v == so && o < lane)) ++rank;
     }
-    // lane o < 9: the old section of the source in offset o
-    const int so_a = lane < 9 ? sp.offp[so] : 0, so_b = lane < 9 ? sp.offp[so + 1] : 0;
+    const int rank4 = __builtin_amdgcn_readlane(rank, 4);
+    const int oA = __builtin_amdgcn_readlane(so_a, 4), oB = __builtin_amdgcn_readlane(so_b, 4);
     // Whether the particle at `slot` of another tile's old section, with
     // tile-relative cell lc, has moved into t: its cell lies one tile off
     // its own in some offset o, and the source of t in offset o is the tile
@@ -324,108 +417,54 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
         const int sa = __shfl(so_a, o, 64), sb = __shfl(so_b, o, 64);
         return o != 4 && (lc & 0xffff) != kTCellRemoved && slot >= sa && slot < sb;
     };
-    // the source of rank q, -1 if there is none (all lanes take part)
-    auto source_of_rank = [&](int q) {
-        int v = -1;
+
+    // ---------------- the lists: first index, length; of a neighbour's list
+    // also its old section's first slot and length
+    const int lA = max(A, oA), lB = min(B, oB);
+    int dbm = 0, dlen = 0, ds0 = 0, dns = 0;
+    {
+        const int m = lane - (W + 2);   // mover lists 0 .. 9
+        int from = 0;                   // the direction whose list this is
 #pragma unroll
         for (int o = 0; o < 9; ++o) {
-            const int so_o = __shfl(so, o, 64), rank_o = __shfl(rank, o, 64), first_o = __shfl(first, o, 64);
-            if (first_o && rank_o == q) v = so_o;
+            const int r = __builtin_amdgcn_readlane(rank, o);
+            if (o != 4 && r + (r > rank4 ? 1 : 0) == m) from = o;
         }
-        return v;
-    };
-
-    // ---------------- list bounds: every load of this stage in flight at once
-    const int nl_mov = 9 * W;
-    int srcv[2], subl[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = lane + 64 * h;
-        const int q = v >= W + 2 && v < W + 2 + nl_mov ? (v - W - 2) / W : -1;
-        subl[h] = v >= W + 2 ? (v - W - 2) % W : v - 1;   // sub-list index (movers; holes: v - 1)
-        srcv[h] = source_of_rank(q);
-    }
-    const int A = sp.off[t], B = sp.off[t + 1];     // new section
-    const int oA = sp.offp[t], oB = sp.offp[t + 1];  // old section
-    int f0[2], f1[2], fc[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = lane + 64 * h;
-        // hole sub-lists read t's record, mover sub-lists their source's (index 0 when unused)
-        const int s = v >= 1 && v <= W ? t : (srcv[h] >= 0 ? srcv[h] : 0);
-        const int w = v >= 1 && v <= W ? v - 1 : (srcv[h] >= 0 ? subl[h] : 0);
-        f0[h] = sp.offp[s];
-        f1[h] = sp.offp[s + 1];
-        fc[h] = sp.cnt[(int64_t)s * kCntStride + kCntSub + w];
-    }
-    int i0 = 0, i1 = 0;
-    if (sp.inj_off) {
-        i0 = sp.n + sp.inj_off[t];
-        i1 = sp.n + sp.inj_off[t + 1];
-    }
-    const int lA = max(A, oA), lB = min(B, oB);
-    // descriptors: kind | src << 2, (base - first index), length, s0, ns
-    int dks[2], dbm[2], dlen[2], ds0[2], dns[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = lane + 64 * h;
-        int kind = kListHoleRange, base = 0, len = 0, src = 0, s0 = 0, ns = 0;
-        if (v == 0) {
-            base = A;
-            len = max(0, min(B, oA) - A);
-        } else if (v <= W) {
+        const int fb = __shfl(lbase, from, 64), fl = __shfl(llen, from, 64);
+        const int fa = __shfl(so_a, from, 64), fe = __shfl(so_b, from, 64);
+        if (lane == 0) {
+            dbm = A;
+            dlen = max(0, min(B, oA) - A);
+        } else if (lane <= W) {
             int wlo, whi;
-            wave_range(oA, oB, v - 1, W, wlo, whi);
-            kind = kListHoleLeav;
-            base = wlo;
-            len = lA < lB ? min(fc[h], whi - wlo) : 0;
-        } else if (v == W + 1) {
-            base = max(A, oB);
-            len = max(0, B - base);
-        } else if (v < W + 2 + nl_mov) {
-            src = srcv[h];
-            const int w = subl[h];
-            kind = kListMoverRange;
-            if (src == t) {
-                if (w == 0) {
-                    base = oA;
-                    len = max(0, min(oB, A) - oA);
-                } else if (w == 1) {
-                    base = max(oA, B);
-                    len = max(0, oB - base);
-                }
-            } else if (src >= 0) {
-                int wlo, whi;
-                wave_range(f0[h], f1[h], w, W, wlo, whi);
-                kind = kListMoverLeav;
-                base = wlo;
-                len = min(fc[h], whi - wlo);
-                s0 = f0[h];
-                ns = f1[h] - f0[h];
-            }
-            src = max(src, 0);
-        } else if (v == W + 2 + nl_mov && sp.inj_off) {
-            kind = kListMoverRange;
-            base = i0;
-            len = max(0, min(i1, A) - i0);
-        } else if (v == W + 3 + nl_mov && sp.inj_off) {
-            kind = kListMoverRange;
-            base = max(i0, B);
-            len = max(0, i1 - base);
+            wave_range(oA, oB, lane - 1, W, wlo, whi);
+            dbm = wlo;
+            dlen = lA < lB ? min(sub, whi - wlo) : 0;
+        } else if (lane == W + 1) {
+            dbm = max(A, oB);
+            dlen = max(0, B - dbm);
+        } else if (m == rank4) {
+            dbm = oA;
+            dlen = max(0, min(oB, A) - oA);
+        } else if (m == rank4 + 1) {
+            dbm = max(oA, B);
+            dlen = max(0, oB - dbm);
+        } else if (m < 10) {
+            dbm = fb;
+            dlen = fl;
+            ds0 = fa;
+            dns = fe - fa;
+        } else if (m == 10 && sp.inj_off) {
+            dbm = i0;
+            dlen = max(0, min(i1, A) - i0);
+        } else if (m == 11 && sp.inj_off) {
+            dbm = max(i0, B);
+            dlen = max(0, i1 - dbm);
         }
-        dks[h] = kind | (src << 2);
-        dbm[h] = base;
-        dlen[h] = len;
-        ds0[h] = s0;
-        dns[h] = ns;
     }
-    // the flat index space: slots 0..63 (first register), then 64..127
-    int tot0, tot1;
-    const int ex0 = wave_exclusive(dlen[0], tot0);
-    const int ex1 = tot0 + wave_exclusive(dlen[1], tot1);
-    const int total = tot0 + tot1;
-    dbm[0] -= ex0;   // candidate k of the list: base + (k - ex) = dbm + k
-    dbm[1] -= ex1;
+    int total;
+    const int ex = wave_exclusive(dlen, total);
+    dbm -= ex;   // candidate k of the list: base + (k - ex) = dbm + k
 
     // the first slot of each pushing wavefront's run of the new section
     // (lane w < W): the holes below it give that run's first hole rank
@@ -435,67 +474,61 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
         wave_range(A, B, lane, W, wlo_mine, whi);
     }
 
-    bool bad = false;
     int nh = 0, nm = 0;
     for (int k0 = 0; k0 < total; k0 += 64 * NB) {
         // ---- the candidates: their lists, then every load in flight at once
-        int at[NB], ks[NB], s0v[NB], nsv[NB], lv[NB];
-        uint32_t v[NB];
+        int at[NB], s0v[NB], nsv[NB], lv[NB];
+        uint32_t v[NB], rec[NB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
             const int k = k0 + 64 * u + lane;
-            const int L0 = find_list(k, ex0), L1 = find_list(k, ex1);
-            const bool hi = k >= tot0;
-            const int L = hi ? L1 : L0;
-            auto pick = [&](const int *f) {
-                const int x0 = __shfl(f[0], L, 64), x1 = __shfl(f[1], L, 64);
-                return hi ? x1 : x0;
-            };
-            lv[u] = k < total ? L + (hi ? 64 : 0) : -1;
-            ks[u] = pick(dks);
-            at[u] = pick(dbm) + k;
-            s0v[u] = pick(ds0);
-            nsv[u] = pick(dns);
-            const int kind = ks[u] & 3;
-            v[u] = 0;
-            if (k < total)
-                v[u] = kind == kListHoleRange || kind == kListMoverRange ? (uint32_t)(int)sp.p.cell[at[u]]
-                                                                         : sp.leav[at[u]];
-            // a sorted state (the window's sort): every particle is in the
-            // tile of its section, its cell relative to it modulo T
-            if (a.rebase && (kind == kListHoleRange || kind == kListMoverRange) &&
-                (v[u] & 0xffffu) != (uint32_t)kTCellRemoved)
-                v[u] = (uint32_t)tcell_pack(tcell_x((int)v[u]) & (T - 1), tcell_y((int)v[u]) & (T - 1));
+            const int L = find_list(k, ex);
+            at[u] = __shfl(dbm, L, 64) + k;
+            s0v[u] = __shfl(ds0, L, 64);
+            nsv[u] = __shfl(dns, L, 64);
+            lv[u] = k < total ? L : -1;
+            v[u] = rec[u] = 0;
+            if (k < total) {
+                const int m = L - (W + 2);
+                if (L >= 1 && L <= W) {
+                    v[u] = gp(sp.leav)[at[u]];
+                } else if (m >= 0 && m < 10 && m != rank4 && m != rank4 + 1) {
+                    const vi2a e = ((const PIC_GLOBAL vi2a *)sp.dlist)[at[u]];
+                    v[u] = (uint32_t)e.x;
+                    rec[u] = (uint32_t)e.y;
+                } else {
+                    v[u] = (uint32_t)(int)gp(sp.p.cell)[at[u]];
+                    // a sorted state (the window's sort): every particle is in the
+                    // tile of its section, its cell relative to it modulo T
+                    if (a.rebase && (v[u] & 0xffffu) != (uint32_t)kTCellRemoved)
+                        v[u] = (uint32_t)tcell_pack(tcell_x((int)v[u]) & (T - 1), tcell_y((int)v[u]) & (T - 1));
+                }
+            }
         }
         // ---- the ballots, in candidate order: holes first, then movers
         int rr[NB];
         unsigned mvf = 0, flf = 0;   // per iteration: a mover of this lane, from the leaver records
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            const int kind = ks[u] & 3, L = lv[u];
+            const int L = lv[u], m = L - (W + 2);
             bool ph = false, pm = false, fl = false;
             int slot = at[u];
             const bool in_t = arrived((int)v[u], slot);
-            if (L >= 0) {
-                if (kind == kListHoleRange) {
-                    ph = !in_t;
-                } else if (kind == kListHoleLeav) {
-                    slot = oA + (int)(v[u] >> 4);
-                    ph = slot >= lA && slot < lB;
-                } else if (kind == kListMoverRange) {
-                    pm = tcell_inside((int)v[u], T);   // t's own slots, or its new particles
+            if (L == 0 || L == W + 1) {
+                ph = !in_t;
+            } else if (L >= 1 && L <= W) {
+                slot = oA + (int)(v[u] >> 4);
+                ph = slot >= lA && slot < lB;
+            } else if (L >= 0 && (m == rank4 || m == rank4 + 1 || m >= 10)) {
+                pm = tcell_inside((int)v[u], T);   // t's own slots, or its new particles
+            } else if (L >= 0) {
+                if ((int)v[u] >= nsv[u] || (int)rec[u] >= nsv[u]) {
+                    bad = true;
                 } else {
-                    const int d = (int)(v[u] & 15u), loc = (int)(v[u] >> 4);
-                    if (loc >= nsv[u] || d > kDirRemoved) {
-                        bad = true;
-                    } else if (d != kDirRemoved) {   // a removed particle is nobody's mover
-                        const int src = ks[u] >> 2;
-                        const int sx = src % ntx, sy = src / ntx;
-                        const int dest = wrap_s(sy + d / 3 - 1, nty) * ntx + wrap_s(sx + d % 3 - 1, ntx);
-                        const int ms = s0v[u] + loc;
-                        pm = dest == t && !(ms >= A && ms < B);
-                        fl = true;
-                    }
+                    const int ms = s0v[u] + (int)v[u];
+                    pm = !(ms >= A && ms < B);
+                    fl = true;
+                    at[u] = s0v[u] + (int)rec[u];
                 }
             }
             const unsigned long long mh = __ballot(ph);
@@ -902,16 +935,29 @@ __global__ void k_init_offsets(const int32_t *__restrict__ cell, int32_t n, int 
     off[t] = lo;
 }
 
-void launch_sort_scan(const SortArgs &a, int n_tiles, hipStream_t s)
+// How the plan gets the new sections: up to one scan block of tiles each plan
+// block counts them all itself (at most 64 blocks then read 2,304 counts each,
+// below the cost of a launch); else from k_sort_count's prefixes, the blocks
+// before its own added by the plan while one load per lane holds them.
+static int scan_mode(int64_t n_blocks)
+{
+    return n_blocks <= 1 ? kScanLocal : (n_blocks <= kScanDirect ? kScanSums : kScanBases);
+}
+
+static void launch_sort_counts(const SortArgs &a, int n_tiles, hipStream_t s)
 {
     const int nb = (n_tiles + kScanBlock - 1) / kScanBlock;
     hipLaunchKernelGGL(k_sort_count, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
-    if (nb <= kScanDirect) {
-        hipLaunchKernelGGL(k_sort_add_direct, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
-        return;
-    }
-    hipLaunchKernelGGL(k_sort_scan_blocks, dim3(a.n_species), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_sort_add_base, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
+    if (nb > kScanDirect) hipLaunchKernelGGL(k_sort_scan_blocks, dim3(a.n_species), dim3(1024), 0, s, a);
+}
+
+void launch_sort_scan(const SortArgs &a, int n_tiles, bool offsets, hipStream_t s)
+{
+    const int nb = (n_tiles + kScanBlock - 1) / kScanBlock;
+    if (offsets || scan_mode(nb) != kScanLocal) launch_sort_counts(a, n_tiles, s);
+    if (!offsets) return;
+    if (nb <= kScanDirect) hipLaunchKernelGGL(k_sort_add_direct, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
+    else hipLaunchKernelGGL(k_sort_add_base, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
 }
 
 // Plan wavefronts (one per tile and species) that fit the device at once with
@@ -919,8 +965,10 @@ void launch_sort_scan(const SortArgs &a, int n_tiles, hipStream_t s)
 // two-iteration plan runs twice as many at once.
 constexpr int64_t kPlanResident = 4096;
 
-void launch_sort_plan(const SortArgs &a, int n_tiles, hipStream_t s)
+void launch_sort_plan(const SortArgs &args, int n_tiles, hipStream_t s)
 {
+    SortArgs a = args;
+    a.scan = scan_mode((n_tiles + kScanBlock - 1) / kScanBlock);
     const dim3 grid((n_tiles + kSortWaves - 1) / kSortWaves, a.n_species);
     if ((int64_t)n_tiles * a.n_species <= kPlanResident)
         hipLaunchKernelGGL(k_sort_plan<kPlanBatch>, grid, dim3(kBlock), 0, s, a);
@@ -951,17 +999,19 @@ void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s)
                            rebase ? 1 : 0);
 }
 
+int batch_scan_mode(int max_blocks) { return max_blocks <= kScanDirect ? kScanSums : kScanBases; }
+
 void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s)
 {
     if (b.n_count == 0) return;
     hipLaunchKernelGGL(k_sort_count_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
-    if (b.max_blocks <= kScanDirect) {
-        hipLaunchKernelGGL(k_sort_add_direct_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
-    } else {
+    if (b.max_blocks > kScanDirect)
         hipLaunchKernelGGL(k_sort_scan_blocks_b, dim3(b.n_scan), dim3(1024), 0, s, b.descs, b.scan_items);
-        hipLaunchKernelGGL(k_sort_add_base_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
-    }
     if (motion) {
+        if (b.max_blocks <= kScanDirect)
+            hipLaunchKernelGGL(k_sort_add_direct_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
+        else
+            hipLaunchKernelGGL(k_sort_add_base_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
         hipLaunchKernelGGL(k_motion_scatter_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
         hipLaunchKernelGGL(k_motion_copy_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
     } else {

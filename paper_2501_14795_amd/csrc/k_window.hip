@@ -23,14 +23,17 @@ __global__ void __launch_bounds__(256) k_zero_column(float *__restrict__ fld, in
 }
 
 // Count records of a step in which nothing moves: all particles of a tile
-// stay (direction 4), no leavers.  One thread per record entry.
-__global__ void __launch_bounds__(256) k_window_records(const int32_t *__restrict__ off, int32_t *__restrict__ cnt,
-                                                        int n_tiles)
+// stay (direction 4), no leavers.  One thread per record entry; and the copy
+// of the old sections for the sort.
+__global__ void __launch_bounds__(256) k_window_records(const int32_t *__restrict__ off, int32_t *__restrict__ offp,
+                                                        int32_t *__restrict__ cnt, int n_tiles)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)n_tiles * kCntStride) return;
     const int t = (int)(i / kCntStride), k = (int)(i % kCntStride);
     cnt[i] = k == 4 ? off[t + 1] - off[t] : 0;
+    if (k == 0) offp[t] = off[t];
+    if (i == 0) offp[n_tiles] = off[n_tiles];
 }
 
 // The tiles of the tile column that holds array column `col`, one per
@@ -119,8 +122,8 @@ void launch_window_remove(int tile, const WindowSpecies &w, int ntx, int nty, in
 {
     if (n_tiles <= 0) return;
     const int64_t entries = (int64_t)n_tiles * kCntStride;
-    hipLaunchKernelGGL(k_window_records, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, w.off, w.cnt,
-                       n_tiles);
+    hipLaunchKernelGGL(k_window_records, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, w.off, w.offp,
+                       w.cnt, n_tiles);
     switch (tile) {
     case 8: hipLaunchKernelGGL((k_window_remove<8>), dim3(nty), dim3(64 * push_waves(8)), 0, s, w, ntx, col); break;
     case 16:

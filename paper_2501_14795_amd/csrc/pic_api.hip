@@ -24,7 +24,7 @@ struct Layout {
     size_t wrem = 0, inj_off[kMaxSpecies] = {};
     size_t off[kMaxSpecies][2] = {}, cnt[kMaxSpecies] = {}, leav[kMaxSpecies] = {};
     size_t hole[kMaxSpecies] = {}, stg[kMaxSpecies][6] = {}, mcount[kMaxSpecies] = {}, bsum[kMaxSpecies] = {};
-    size_t lrec[kMaxSpecies] = {}, srec[kMaxSpecies] = {}, fcount[kMaxSpecies] = {}, fbase[kMaxSpecies] = {};
+    size_t lrec[kMaxSpecies] = {}, srec[kMaxSpecies] = {}, dlist[kMaxSpecies] = {}, fcount[kMaxSpecies] = {}, fbase[kMaxSpecies] = {};
     size_t lcell[kMaxSpecies] = {};
     size_t total = 0;
 };
@@ -139,6 +139,7 @@ Layout make_layout(const pic_config *c)
         // leaver records; the full re-sort also borrows the region as six
         // arrays of n values (lp_view)
         L.lrec[s] = take(n * sizeof(LeaverRec) + 6 * kAlign);
+        L.dlist[s] = take(n * sizeof(uint2));   // the leavers by direction
         L.hole[s] = take(n * sizeof(int32_t));
         // mover staging: the in-place sort's 32-byte records (every
         // simulation: the moving window's sort is the in-place one; also the
@@ -146,7 +147,7 @@ Layout make_layout(const pic_config *c)
         L.srec[s] = take(n * sizeof(LeaverRec));
         if (c->flags & PIC_FLAG_MOTION_SORT)
             for (int k = 0; k < 6; ++k) L.stg[s][k] = take(n * (k == 0 ? sizeof(int16_t) : sizeof(float)));
-        L.mcount[s] = take((size_t)3 * n_tiles * sizeof(int32_t));   // movers (motion sort: class bases)
+        L.mcount[s] = take((size_t)3 * n_tiles * sizeof(int32_t));   // movers; new counts and their prefix
         L.fcount[s] = take((size_t)n_tiles * sizeof(int32_t));       // pending fill per tile
         L.fbase[s] = take((size_t)n_tiles * push_waves(T) * sizeof(int32_t));
         L.bsum[s] = take((size_t)(n_tiles / kScanBlock + 1) * sizeof(int32_t));
@@ -194,6 +195,7 @@ struct pic_sim {
         Parts stg;         // the motion-class sort's staging (null without PIC_FLAG_MOTION_SORT)
         LeaverRec *srec;   // the in-place sort's mover staging (every simulation)
         LeaverRec *lrec;   // the push's leaver records
+        uint2 *dlist;      // the leavers by direction
         GParts lp;         // the same memory as six arrays of n values (the initial grouping's scratch)
         int32_t *mcount;
         int32_t *fcount;   // holes whose fill a deferred sort left to the next push
@@ -458,6 +460,8 @@ PushArgs push_args(const pic_sim *S, bool bh)
         d.cnt = S->sp[s].cnt;
         d.leav = S->sp[s].leav;
         d.lrec = S->sp[s].lrec;
+        d.dlist = (c.flags & PIC_FLAG_MOTION_SORT) ? nullptr : S->sp[s].dlist;
+        d.offp = S->sp[s].offp;
         d.fcount = S->sp[s].fcount;
         d.fbase = S->sp[s].fbase;
         d.fhole = S->sp[s].hole;
@@ -519,6 +523,7 @@ SortArgs sort_args(const pic_sim *S, bool defer = false)
     a.ntx = S->ntx;
     a.nty = S->nty;
     a.tile = S->tile;
+    a.waves = push_waves(S->tile);
     a.n_tiles = S->n_tiles;
     a.n_species = c.n_species;
     for (int s = 0; s < c.n_species; ++s) {
@@ -539,8 +544,11 @@ SortArgs sort_args(const pic_sim *S, bool defer = false)
         d.offp = P.offp;
         d.cnt = P.cnt;
         d.leav = P.leav;
+        d.dlist = P.dlist;
         d.hole = P.hole;
         d.mcount = P.mcount;
+        d.pre = P.mcount + S->n_tiles;
+        d.cnew = P.mcount + 2 * (size_t)S->n_tiles;
         d.fcount = P.fcount;
         d.fbase = P.fbase;
         d.bsum = P.bsum;
@@ -751,6 +759,7 @@ int init_sim(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream,
         P.stg = motion ? parts_at(L.stg[s]) : Parts{};
         P.srec = (LeaverRec *)(w + L.srec[s]);
         P.lrec = (LeaverRec *)(w + L.lrec[s]);
+        P.dlist = (uint2 *)(w + L.dlist[s]);
         {
             size_t o[6];
             const size_t n = (size_t)(cfg->species[s].cap ? cfg->species[s].cap : cfg->species[s].n);
@@ -880,7 +889,7 @@ static int motion_sort(pic_sim *S, hipStream_t stream, bool defer)
     const SortArgs a = sort_args(S, defer);
     {
         Timed t(S, PIC_KERNEL_SORT_SCAN, stream);
-        launch_sort_scan(a, S->n_tiles, stream);
+        launch_sort_scan(a, S->n_tiles, true, stream);
     }
     {
         Timed t(S, PIC_KERNEL_SORT_PLAN, stream);
@@ -903,7 +912,7 @@ static int sort_after_push(pic_sim *S, hipStream_t stream, bool defer)
     const SortArgs a = sort_args(S, defer);
     {
         Timed t(S, PIC_KERNEL_SORT_SCAN, stream);
-        launch_sort_scan(a, S->n_tiles, stream);
+        launch_sort_scan(a, S->n_tiles, false, stream);
     }
     {
         Timed t(S, PIC_KERNEL_SORT_PLAN, stream);
@@ -1004,6 +1013,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
         WindowSpecies ws;
         ws.p = a.sp[s].p;
         ws.off = P.off;
+        ws.offp = P.offp;
         ws.cnt = P.cnt;
         ws.leav = P.leav;
         ws.removed = S->wrem + s;
@@ -1013,7 +1023,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
     if (rc == PIC_OK) rc = hip_ok(hipGetLastError());
     if (rc) return rc;
     // 4. the canonical re-sort, the new particles taken as appended
-    launch_sort_scan(a, S->n_tiles, stream);
+    launch_sort_scan(a, S->n_tiles, false, stream);
     launch_sort_plan(a, S->n_tiles, stream);
     launch_sort_scatter(a, S->n_tiles, stream);
     rc = hip_ok(hipGetLastError());
@@ -1529,6 +1539,7 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
         hp[i] = push_args(S, true);
         hj[i] = jreduce_args(S);
         hs[i] = sort_args(S, !(S->cfg.flags & PIC_FLAG_MOTION_SORT));
+        hs[i].scan = batch_scan_mode(B->max_blocks);
         hf[i] = field_args(S, S->cfg.j_filter == 0, true);
         hfl[i] = filter_args(S, 0);
         hfl[n + i] = filter_args(S, 1);

@@ -10,19 +10,25 @@
 
 namespace pic {
 
+// kScanLocal: each plan block counts all tiles; kScanSums: from the counts'
+// prefixes and the scan blocks' totals; kScanBases: from those and the
+// totals' exclusive prefix
+enum : int { kScanLocal = 0, kScanSums = 1, kScanBases = 2 };
+
 struct SortSpecies {
     Parts p;              // the particle arrays (tile-relative cells)
     int32_t *gcell;       // the caller's cell array: whole-grid cells, written by the publish
     const LeaverRec *lrec;   // leaver particle data written by the push kernel
     Parts stg;            // the motion-class sort's staging, [n]: every particle at its new slot
     LeaverRec *srec;      // the in-place sort's mover staging, [n]: tile t's movers at off[t] + k, in hole order
-    int32_t *off;         // tile_offset: the recount's first pass keeps it in offp and the scan
-                          // writes the new one in its place
-    int32_t *offp;        // the tile_offset before the sort (scratch)
+    int32_t *off;         // tile_offset: the sort writes the new one
+    const int32_t *offp;  // the tile_offset before the sort: a copy the push (or the window) made
     const int32_t *cnt;
     const uint32_t *leav;
+    const uint2 *dlist;   // the leavers by direction of motion (SpeciesDev::dlist)
+    int32_t *pre, *cnew;  // [n_tiles]: new counts, and their prefix within a scan block
     int32_t *hole;        // [n]: tile t's holes, ascending, at off[t] + k
-    int32_t *mcount;      // [n_tiles]: movers (the motion-class sort: [3][n_tiles] class bases)
+    int32_t *mcount;      // [n_tiles]: movers
     int32_t *fcount;      // [n_tiles]: holes whose fill is pending (the next push fills them), else 0
     int32_t *fbase;       // [n_tiles][W]: first pending hole of each push wavefront's run
     int32_t *bsum;        // [n_tiles / kScanBlock + 1] block totals of the tile scan
@@ -38,6 +44,8 @@ struct SortSpecies {
 struct SortArgs {
     int *err;
     int nx, ny, ntx, nty, tile;
+    int waves;            // leaver sub-lists per tile: the push's wavefronts per tile
+    int scan;             // where the plan gets the new sections (kScan*)
     int n_tiles;
     int n_species;
     int defer;            // 1: the scatter leaves the holes to the next push (pic_step); the
@@ -80,7 +88,9 @@ void launch_push_batch(int tile, int replicas, int jmode, int dmode, int halo, i
 void launch_j_reduce_batch(int tile, int halo, const JReduceArgs *descs, const int4 *items, int n_items,
                            hipStream_t s);
 void launch_set_int(int *p, int v, hipStream_t s);
-void launch_sort_scan(const SortArgs &a, int n_tiles, hipStream_t s);
+// the recount; offsets: tile_offset too (the motion-class sort; else the plan
+// forms it)
+void launch_sort_scan(const SortArgs &a, int n_tiles, bool offsets, hipStream_t s);
 void launch_sort_plan(const SortArgs &a, int n_tiles, hipStream_t s);
 void launch_sort_scatter(const SortArgs &a, int n_tiles, hipStream_t s);
 void launch_fill(const SortArgs &a, int n_tiles, hipStream_t s);
@@ -102,6 +112,8 @@ struct SortBatch {
 };
 // launch_settle for every member
 void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s);
+// SortArgs::scan of the members of a batch
+int batch_scan_mode(int max_blocks);
 // motion: the motion-class sort (PIC_FLAG_MOTION_SORT) instead of the in-place one
 void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s);
 // the motion-class sort after the recount and scan: every particle into the
@@ -141,6 +153,7 @@ void launch_zero_i32(int32_t *p, int n, hipStream_t s);
 struct WindowSpecies {
     Parts p;                     // tile-relative cells
     const int32_t *off;
+    int32_t *offp;      // a copy of off for the sort
     int32_t *cnt;
     uint32_t *leav;
     int32_t *removed;   // device count of the particles that left

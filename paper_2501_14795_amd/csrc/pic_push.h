@@ -105,7 +105,7 @@ constexpr int push_lds_bytes(int T, int R, int JM, int H = 1)
 {
     return (T + 2 * H) * (T + 2 * H) * (push_packed(T) ? 48 : 24) +
            R * 3 * (T + 2 * H + 1) * (T + 2 * H + 1) * (JM == kJFixed ? 8 : 4) +
-           kMaxSpecies * (9 + push_waves(T)) * 4 + push_waves(T) * 6 * kMotionBuf * 4 +
+           kMaxSpecies * (9 * push_waves(T) + push_waves(T)) * 4 + push_waves(T) * 6 * kMotionBuf * 4 +
            (push_packed(T) ? push_waves(T) * 7 * kLeaverBuf * 4 : 0) + push_waves(T) * 64 * 4;
 }
 
@@ -173,6 +173,8 @@ struct __attribute__((aligned(32))) LeaverRec {
 // assignment)
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef float vf2 __attribute__((ext_vector_type(2)));
+typedef int32_t vi4a __attribute__((ext_vector_type(4)));
+typedef int32_t vi2a __attribute__((ext_vector_type(2)));
 
 // Write one leaver record as two vector stores (16 + 8 bytes).
 __device__ __forceinline__ void put_leaver(LeaverRec *r, int64_t q, int cell, float x, float y, float ux, float uy,
@@ -190,6 +192,10 @@ struct SpeciesDev {
     int32_t *cnt;         // [n_tiles][kCntStride]
     uint32_t *leav;       // [n]: leaver sub-lists, (slot - off[t]) << 4 | direction
     LeaverRec *lrec;      // [n]: the leavers' new particle data, same positions as leav
+    uint2 *dlist;         // [n]: tile t's leavers from off[t] on, by direction of motion, each
+                          // direction in slot order: (slot, position in leav), both relative to off[t];
+                          // null: not wanted (the motion-class sort)
+    int32_t *offp;        // a copy of off for the sort, which rewrites off
     // a fill left by the last sort: tile t's fcount[t] holes, slots fhole[off[t] + r]
     // ascending, take the staged particles fsrc[off[t] + r]; wavefront w's first
     // is rank fbase[t W + w].  The push zeroes fcount[t].
