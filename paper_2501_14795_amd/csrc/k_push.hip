@@ -755,6 +755,11 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     __shared__ int s_wl[kMaxSpecies][W];
     __shared__ uint32_t s_pq[W][6][kMotionBuf];   // queued face-crossing motions
     __shared__ int s_fill[W][64];                  // pending holes of the chunk being loaded
+    // per species: the tile's section [begin, end) and its pending fill, and
+    // each wavefront's first hole of it; read with the halo, so that neither
+    // the particle loop's start nor the records after it wait for memory again
+    __shared__ int s_sec[kMaxSpecies][3];
+    __shared__ int s_fb[kMaxSpecies][W];
 
     const int tx = tile % a.ntx, ty = tile / a.ntx;
     const int gx0 = tx * T, gy0 = ty * T;
@@ -764,6 +769,14 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t plane = (int64_t)a.nx * a.ny;
 
+    // (kMaxSpecies W <= NT; the descriptor index is clamped to the species there are)
+    const int qs = min(tid / W, a.n_species - 1), qw = tid % W;
+    int sec = 0, sfb = 0;
+    if (tid < a.n_species * W) {
+        const PIC_GLOBAL int32_t *v = qw < 2 ? gp(a.sp[qs].off) + tile + qw : gp(a.sp[qs].fcount) + tile;
+        if (qw < 3) sec = *v;
+        sfb = gp(a.sp[qs].fbase)[(int64_t)tile * W + qw];
+    }
     for (int e = tid; e < NE * NE; e += NT) {
         const int r = e / NE, c = e - r * NE;
         const int64_t row = (int64_t)wrapi(gy0 - H + r, a.ny) * a.nx;
@@ -784,6 +797,10 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     }
     for (int e = tid; e < R * 3 * JP; e += NT) (&s_j[0][0])[e] = Acc(0);
     for (int e = tid; e < kMaxSpecies * W * 9; e += NT) (&s_dir[0][0][0])[e] = 0;
+    if (tid < a.n_species * W) {
+        if (qw < 3) s_sec[qs][qw] = sec;
+        s_fb[qs][qw] = sfb;
+    }
     __syncthreads();
 
     Acc *sj = s_j[R > 1 ? lane % R : 0];
@@ -797,7 +814,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
 
     for (int s = 0; s < a.n_species; ++s) {
         const SpeciesDev sp = a.sp[s];
-        const int begin = gp(sp.off)[tile], end = gp(sp.off)[tile + 1];
+        const int begin = __builtin_amdgcn_readfirstlane(s_sec[s][0]), end = __builtin_amdgcn_readfirstlane(s_sec[s][1]);
         int lo, hi;
         wave_range(begin, end, wave, W, lo, hi);
         int nleav = 0;   // wavefront-uniform
@@ -818,11 +835,11 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
             // this run's hole slots, one per lane (fhw: the slot of rank
             // fhb + lane), the next rank not yet placed (fhp) and its slot
             // (fnext, INT_MAX once none is left).  All uniform but fhw.
-            const int nfill = gp(sp.fcount)[tile];
+            const int nfill = __builtin_amdgcn_readfirstlane(s_sec[s][2]);
             const PIC_GLOBAL int32_t *fhole = gp(sp.fhole) + begin;
             int fhb = 0, fhp = 0, fhw = INT_MAX, fnext = INT_MAX;
             if (nfill > 0) {
-                fhb = fhp = gp(sp.fbase)[(int64_t)tile * W + wave];
+                fhb = fhp = __builtin_amdgcn_readfirstlane(s_fb[s][wave]);
                 fhw = fhb + lane < nfill ? fhole[fhb + lane] : INT_MAX;
                 fnext = fhp < nfill ? __builtin_amdgcn_readfirstlane(fhw) : INT_MAX;
             }
@@ -978,66 +995,36 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
         if (lane == 0) s_wl[s][wave] = nleav;
     }
     __syncthreads();
-    // the fill the last sort left is done (every wavefront has read its count)
-    if (tid < a.n_species && gp(a.sp[tid].fcount)[tile] != 0) gp(a.sp[tid].fcount)[tile] = 0;
+    // the fill the last sort left is done
+    if (tid < a.n_species && s_sec[tid][2] != 0) gp(a.sp[tid].fcount)[tile] = 0;
     // the old sections, for the sort
     if (tid < a.n_species) {
-        gp(a.sp[tid].offp)[tile] = gp(a.sp[tid].off)[tile];
-        if (tile == a.ntx * a.nty - 1) gp(a.sp[tid].offp)[tile + 1] = gp(a.sp[tid].off)[tile + 1];
+        gp(a.sp[tid].offp)[tile] = s_sec[tid][0];
+        if (tile == a.ntx * a.nty - 1) gp(a.sp[tid].offp)[tile + 1] = s_sec[tid][1];
     }
 
-    // The tile's leavers by direction, for the sort: each wavefront places its
-    // sub-list's entries behind those of the wavefronts before it (lane d: the
-    // next position of direction d).  About 60 instructions per 64 leavers here
-    // spare the sort plan three of four candidates it would read otherwise.
-    for (int s = 0; s < a.n_species; ++s) {
-        const int mine = s_wl[s][wave];   // wavefront-uniform
-        const SpeciesDev &sp = a.sp[s];
-        if (mine == 0 || !sp.dlist) continue;
-        const int begin = gp(sp.off)[tile], end = gp(sp.off)[tile + 1];
-        int lo, hi;
-        wave_range(begin, end, wave, W, lo, hi);
-        int pos = 0, all = 0;
-        if (lane < 9)
-            for (int w = 0; w < W; ++w) {
-                const int v = s_dir[s][w][lane];
-                pos += w < wave ? v : 0;
-                all += v;
-            }
+    // the first 64 entries of the wavefront's leaver sub-lists of two species,
+    // on their way while the current is written out
+    uint32_t lpre[2] = {0u, 0u};
 #pragma unroll
-        for (int d = 0; d < 9; ++d) {
-            const int v = __builtin_amdgcn_readlane(all, d);
-            if (d < lane) pos += v;
+    for (int s = 0; s < 2; ++s)
+        if (s < a.n_species && a.sp[s].dlist && lane < s_wl[s][wave]) {
+            int lo, hi;
+            wave_range(s_sec[s][0], s_sec[s][1], wave, W, lo, hi);
+            lpre[s] = gp(a.sp[s].leav)[lo + lane];
         }
-        for (int c0 = 0; c0 < mine; c0 += 64) {
-            const bool in = c0 + lane < mine;
-            const int e = lo + c0 + lane;
-            const uint32_t v = in ? gp(sp.leav)[e] : 0u;
-            const int d = in ? (int)(v & 15u) : 9;
-            int at = 0, taken = 0;
-#pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                const unsigned long long m = __ballot(d == k);
-                if (d == k) at = lane_rank(m);
-                if (lane == k) taken = __popcll(m);
-            }
-            at += __shfl(pos, d, 64);
-            if (in) ((PIC_GLOBAL vi2a *)sp.dlist)[(int64_t)begin + at] = vi2a{(int)(v >> 4), e - begin};
-            pos += taken;
-        }
-    }
 
     // the int64 current sums are exact while the tile holds fewer than 2^31
     // particles over all species
     if (JM == kJFixed && tid == 0) {
         int64_t total = 0;
-        for (int s = 0; s < a.n_species; ++s) total += gp(a.sp[s].off)[tile + 1] - gp(a.sp[s].off)[tile];
+        for (int s = 0; s < a.n_species; ++s) total += s_sec[s][1] - s_sec[s][0];
         if (total >= (int64_t(1) << 31)) set_err(a.err, kErrOverflow);
     }
     // per-tile count records
     if (tid < a.n_species * kCntStride) {
         const int s = tid / kCntStride, k = tid % kCntStride;
-        const int n = gp(a.sp[s].off)[tile + 1] - gp(a.sp[s].off)[tile];
+        const int n = s_sec[s][1] - s_sec[s][0];
         int leavers = 0;
         for (int w = 0; w < W; ++w) leavers += s_wl[s][w];
         int v = 0;
@@ -1092,13 +1079,66 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                 bz = s_bz[e];
             }
             const BCell b = faraday_half(bx, by, bz, ex, ex_y, ey, ey_x, ez, ez_x, ez_y, a.hdx, a.hdy);
+            // the old E on the edge columns and rows (a tile starts at a
+            // multiple of 8 cells, and at one edge column at most)
+            if (a.eedge && i == 0 && gx0 % kEdgeX == 0) {
+                PIC_GLOBAL float *d = gp(a.eedge) + edge_col(a.ny, gx0 / kEdgeX, gy0 + j);
+                d[0] = ey;
+                d[a.ny] = ez;
+            }
+            if (a.eedge && j % kEdgeY == 0) {
+                PIC_GLOBAL float *d = gp(a.eedge) + edge_row(a.nx, a.ny, (gy0 + j) / kEdgeY, gx0 + i);
+                d[0] = ex;
+                d[a.nx] = ez;
+            }
             const int64_t g = (int64_t)(gy0 + j) * a.nx + (gx0 + i);
             bh[g] = b.x;
             bh[plane + g] = b.y;
             bh[2 * plane + g] = b.z;
         }
     }
-
+    // The tile's leavers by direction, for the sort: each wavefront places its
+    // sub-list's entries behind those of the wavefronts before it (lane d: the
+    // next position of direction d).  About 60 instructions per 64 leavers here
+    // spare the sort plan three of four candidates it would read otherwise.
+    for (int s = 0; s < a.n_species; ++s) {
+        const int mine = s_wl[s][wave];   // wavefront-uniform
+        const SpeciesDev &sp = a.sp[s];
+        if (mine == 0 || !sp.dlist) continue;
+        const int begin = s_sec[s][0];
+        int lo, hi;
+        wave_range(begin, s_sec[s][1], wave, W, lo, hi);
+        int pos = 0, all = 0;
+        if (lane < 9)
+            for (int w = 0; w < W; ++w) {
+                const int v = s_dir[s][w][lane];
+                pos += w < wave ? v : 0;
+                all += v;
+            }
+#pragma unroll
+        for (int d = 0; d < 9; ++d) {
+            const int v = __builtin_amdgcn_readlane(all, d);
+            if (d < lane) pos += v;
+        }
+        for (int c0 = 0; c0 < mine; c0 += 64) {
+            const bool in = c0 + lane < mine;
+            const int e = lo + c0 + lane;
+            uint32_t v = 0u;
+            if (s < 2 && c0 == 0) v = s == 0 ? lpre[0] : lpre[1];
+            else if (in) v = gp(sp.leav)[e];
+            const int d = in ? (int)(v & 15u) : 9;
+            int at = 0, taken = 0;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const unsigned long long m = __ballot(d == k);
+                if (d == k) at = lane_rank(m);
+                if (lane == k) taken = __popcll(m);
+            }
+            at += __shfl(pos, d, 64);
+            if (in) ((PIC_GLOBAL vi2a *)sp.dlist)[(int64_t)begin + at] = vi2a{(int)(v >> 4), e - begin};
+            pos += taken;
+        }
+    }
 }
 
 // Register budget: the LDS fit (push_min_waves), and at most two waves per

@@ -35,7 +35,7 @@
 // (the alternative of Sec. 4.3), the conversions between the caller's
 // whole-grid cells and the 16-bit ones, and the tile offsets of caller
 // particles at initialisation.
-#include "pic_internal.h"
+#include "pic_eb.h"
 
 namespace pic {
 
@@ -311,6 +311,7 @@ __device__ __forceinline__ bool tcell_inside(int lc, int T)
 // wavefronts, so fewer registers (more wavefronts per SIMD) count more
 constexpr int kPlanBatch = 6;
 constexpr int kPlanBatchB = 2;
+constexpr int kPlanBatchF = 2;   // beside the field half
 static_assert(kMaxWaves + 14 <= 32, "sort plan lists");
 
 template <int NB = kPlanBatch>
@@ -522,7 +523,7 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
             } else if (L >= 0 && (m == rank4 || m == rank4 + 1 || m >= 10)) {
                 pm = tcell_inside((int)v[u], T);   // t's own slots, or its new particles
             } else if (L >= 0) {
-                if ((int)v[u] >= nsv[u] || (int)rec[u] >= nsv[u]) {
+                if (v[u] >= (uint32_t)nsv[u] || rec[u] >= (uint32_t)nsv[u]) {
                     bad = true;
                 } else {
                     const int ms = s0v[u] + (int)v[u];
@@ -842,6 +843,59 @@ __global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int rebase)
 }
 template <int NB>
 __global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit<NB>(a, blockIdx.y, blockIdx.x); }
+
+// The plan and the field half (of a large grid its E step) in one launch: they touch disjoint data, and
+// the plan's wavefronts, which mostly wait, share the chip with the field
+// half's stream.  n_plan plan blocks, one after every `every` - 1 others.
+// (As two chains on two streams the same work paid for the second chain's
+// launches and two event waits: a 64 x 64 step 53 us, now 38; a 512^2 two-beam
+// step 383, now 366.)
+struct PlanMix {
+    int n_plan, every;
+    // the block's plan index, or -1 and its field index in `field`
+    __device__ __forceinline__ int plan_of(int b, int &field) const
+    {
+        const int p = b / every;
+        if (b - p * every == 0 && p < n_plan) return p;
+        field = b - min(n_plan, p + 1);
+        return -1;
+    }
+};
+static PlanMix plan_mix(int n_plan, int n_field) { return PlanMix{n_plan, std::max(1, (n_plan + n_field) / n_plan)}; }
+
+template <int NB, bool FUSED, bool FOLD, int T, int H>
+__global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs f, PlanMix mix)
+{
+    int q;
+    const int p = mix.plan_of(blockIdx.x, q);
+    if (p >= 0) {
+        if (threadIdx.x >= kBlock) return;   // the plan's block is smaller (an ended wavefront holds up no barrier)
+        const int groups = mix.n_plan / a.n_species;
+        sort_plan_unit<NB>(a, p / groups, p % groups);
+    } else if constexpr (FUSED) {
+        const int cols = eb_cols(f.nx);
+        field_eb_region<FOLD, T, H>(f, q % cols, q / cols);
+    } else {
+        field_e_block<FOLD, T, H>(f, q);
+    }
+}
+
+template <int NB, bool FOLD, int T, int H>
+__global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd, const int4 *si, const FieldArgs *fd,
+                                                         const int4 *fi, PlanMix mix)
+{
+    int q;
+    const int p = mix.plan_of(blockIdx.x, q);
+    if (p >= 0) {
+        if (threadIdx.x >= kBlock) return;
+        const int4 w = si[p];
+        sort_plan_unit<NB>(sd[w.x], w.y, w.z);
+    } else {
+        const int4 w = fi[q];
+        field_eb_region<FOLD, T, H>(fd[w.x], w.y, w.z);
+    }
+}
+
 __global__ void __launch_bounds__(kBlock) k_sort_scatter(SortArgs a) { sort_scatter_unit(a, blockIdx.y, blockIdx.x); }
 // single simulation: one tile per block
 __global__ void __launch_bounds__(kBlock) k_motion_scatter(SortArgs a) { motion_scatter_unit(a, blockIdx.y, blockIdx.x, 1); }
@@ -871,11 +925,6 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_add_base_b(const SortArgs *
 {
     const int4 w = it[blockIdx.x];
     sort_add_unit(d[w.x], w.y, w.z);
-}
-__global__ void __launch_bounds__(kBlock) k_sort_plan_b(const SortArgs *d, const int4 *it)
-{
-    const int4 w = it[blockIdx.x];
-    sort_plan_unit<kPlanBatchB>(d[w.x], w.y, w.z);
 }
 // the kSortWaves tiles of an item side by side, a quarter of the block each
 __global__ void __launch_bounds__(kSettleBlock) k_settle_b(const SortArgs *d, const int4 *it, int rebase)
@@ -1001,23 +1050,71 @@ void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s)
 
 int batch_scan_mode(int max_blocks) { return max_blocks <= kScanDirect ? kScanSums : kScanBases; }
 
-void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s)
+void launch_sort_scan_batch(const SortBatch &b, bool offsets, hipStream_t s)
 {
     if (b.n_count == 0) return;
     hipLaunchKernelGGL(k_sort_count_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
     if (b.max_blocks > kScanDirect)
         hipLaunchKernelGGL(k_sort_scan_blocks_b, dim3(b.n_scan), dim3(1024), 0, s, b.descs, b.scan_items);
-    if (motion) {
-        if (b.max_blocks <= kScanDirect)
-            hipLaunchKernelGGL(k_sort_add_direct_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
-        else
-            hipLaunchKernelGGL(k_sort_add_base_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
-        hipLaunchKernelGGL(k_motion_scatter_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
-        hipLaunchKernelGGL(k_motion_copy_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
-    } else {
-        // the batched in-place sort is deferred: the next batched push fills the holes
-        hipLaunchKernelGGL(k_sort_plan_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
+    if (!offsets) return;
+    if (b.max_blocks <= kScanDirect)
+        hipLaunchKernelGGL(k_sort_add_direct_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
+    else
+        hipLaunchKernelGGL(k_sort_add_base_b, dim3(b.n_count), dim3(kScanBlock), 0, s, b.descs, b.count_items);
+}
+
+void launch_motion_batch(const SortBatch &b, hipStream_t s)
+{
+    if (b.n_plan == 0) return;
+    hipLaunchKernelGGL(k_motion_scatter_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
+    hipLaunchKernelGGL(k_motion_copy_b, dim3(b.n_plan), dim3(kBlock), 0, s, b.descs, b.plan_items);
+}
+
+namespace {
+
+template <int NB>
+struct PlanFieldLaunch {
+    const SortArgs *a;       // single
+    const FieldArgs *f;
+    int n_plan, n_field;
+    const SortBatch *b;      // batched
+    const FieldArgs *fd;
+    const int4 *fi;
+    hipStream_t s;
+    template <bool FOLD, int T, int H>
+    void run() const
+    {
+        const PlanMix mix = plan_mix(n_plan, n_field);
+        const dim3 grid(n_plan + n_field);
+        if (a && f->eedge) {
+            hipLaunchKernelGGL((k_plan_field<NB, true, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
+        } else if (a) {   // a large grid: E here, the second B half step after it
+            hipLaunchKernelGGL((k_plan_field<NB, false, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
+            launch_field_b(*f, s);
+        } else
+            hipLaunchKernelGGL((k_plan_field_b<NB, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, b->descs, b->plan_items, fd,
+                               fi, mix);
     }
+};
+
+}  // namespace
+
+void launch_plan_and_field(const SortArgs &args, int n_tiles, const FieldArgs &f, int tile, int halo, hipStream_t s)
+{
+    SortArgs a = args;
+    a.scan = scan_mode((n_tiles + kScanBlock - 1) / kScanBlock);
+    const int n_plan = (n_tiles + kSortWaves - 1) / kSortWaves * a.n_species;
+    const int n_field = f.eedge ? eb_cols(f.nx) * eb_rows(f.ny) : e_blocks(f.nx, f.ny);
+    eb_dispatch(PlanFieldLaunch<kPlanBatchF>{&a, &f, n_plan, n_field, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,
+                tile, halo);
+}
+
+void launch_plan_and_field_batch(const SortBatch &b, const FieldArgs *fields, const int4 *regions, int n_regions,
+                                 bool fold, int tile, int halo, hipStream_t s)
+{
+    if (b.n_plan == 0) return;
+    eb_dispatch(PlanFieldLaunch<kPlanBatchB>{nullptr, nullptr, b.n_plan, n_regions, &b, fields, regions, s}, fold, tile,
+                halo);
 }
 
 void launch_motion_scatter(const SortArgs &a, int n_tiles, hipStream_t s)

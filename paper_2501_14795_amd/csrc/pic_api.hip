@@ -9,7 +9,7 @@
 #include <new>
 #include <vector>
 
-#include "pic_internal.h"
+#include "pic_eb.h"
 
 using namespace pic;
 
@@ -20,7 +20,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) & ~(kAlign - 1); }
 
 struct Layout {
-    size_t err = 0, stg_live = 0, dacc = 0, cacc = 0, jtile = 0, bh = 0, rho_prev = 0, rho_now = 0, jf = 0, rho_tmp = 0;
+    size_t err = 0, stg_live = 0, dacc = 0, cacc = 0, jtile = 0, bh = 0, eedge = 0, rho_prev = 0, rho_now = 0, jf = 0, rho_tmp = 0;
     size_t wrem = 0, inj_off[kMaxSpecies] = {};
     size_t off[kMaxSpecies][2] = {}, cnt[kMaxSpecies] = {}, leav[kMaxSpecies] = {};
     size_t hole[kMaxSpecies] = {}, stg[kMaxSpecies][6] = {}, mcount[kMaxSpecies] = {}, bsum[kMaxSpecies] = {};
@@ -117,6 +117,7 @@ Layout make_layout(const pic_config *c)
     const int NJ = T + 2 * halo_of(c) + 1;   // current halo nodes per axis
     L.jtile = take((size_t)n_tiles * 3 * NJ * NJ * sizeof(float));
     L.bh = take(nodes * 3 * sizeof(float));   // B after the first half step (pic_step)
+    L.eedge = take(edge_size(c->nx, c->ny) * sizeof(float));   // the old E for the field half in one launch
     L.rho_prev = take(nodes * sizeof(double));
     L.rho_now = take(nodes * sizeof(double));
     if (c->j_filter > 0) {
@@ -169,6 +170,7 @@ struct pic_sim {
     unsigned long long *cacc;
     float *jtile;
     float *bh;          // B after the step's first half step, written by pic_step's push
+    float *eedge;       // the edge strips of E, likewise
     double *rho_prev, *rho_now;
     float *jf;          // filter partner of the J planes (j_filter > 0)
     double *rho_tmp;    // filter partner of rho_now (j_filter > 0)
@@ -177,11 +179,6 @@ struct pic_sim {
     int halo;           // the push kernel's halo pad (the cadence, + 1 for the quadratic shape)
     int since_sort;     // pushes since the last sort
     int32_t *wrem;      // moving window: particles that left, per species
-    // pic_step's second stream: the field half of a step (J fold, filter,
-    // field advance) runs there beside the sort, forked from and joined back
-    // into the caller's stream with these two events
-    hipStream_t side;
-    hipEvent_t ev_fork, ev_join;
     int64_t cap[kMaxSpecies];
     int device;         // the device current at pic_init
     bool have_snapshot;
@@ -241,18 +238,6 @@ int scratch_address(int dev, void **ptr)
     }
     *ptr = g_scratch_ptr[dev];
     return PIC_OK;
-}
-
-void release_side(pic_sim *s)
-{
-    if (s->side) {
-        (void)hipStreamSynchronize(s->side);
-        (void)hipStreamDestroy(s->side);
-    }
-    if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
-    if (s->ev_join) (void)hipEventDestroy(s->ev_join);
-    s->side = nullptr;
-    s->ev_fork = s->ev_join = nullptr;
 }
 
 hipEvent_t take_event(pic_sim *s)
@@ -416,6 +401,13 @@ int solve_gauss_in(pic_sim *S, double *d, double tol, int max_iter, pic_gauss_ou
 }
 
 
+// The edge strips of a simulation stepped on its own: null where its field
+// half is two launches (a batch always uses one).
+float *edges(const pic_sim *S)
+{
+    return (int64_t)S->cfg.nx * S->cfg.ny <= kFuseCells ? S->eedge : nullptr;
+}
+
 // Kernel arguments of one simulation (identical every step: the sort writes
 // the new tile_offset in place).
 PushArgs push_args(const pic_sim *S, bool bh)
@@ -425,6 +417,7 @@ PushArgs push_args(const pic_sim *S, bool bh)
     memset(&a, 0, sizeof(a));
     a.fld = S->buf.fields;
     a.bh = bh ? S->bh : nullptr;
+    a.eedge = edges(S);
     a.hdx = (float)(0.5 * c.dt / c.dx);
     a.hdy = (float)(0.5 * c.dt / c.dy);
     a.jtile = S->jtile;
@@ -569,6 +562,7 @@ FieldArgs field_args(const pic_sim *S, bool fold, bool bh)
     f.fld = S->buf.fields;
     f.jtile = fold ? S->jtile : nullptr;
     f.bh = bh ? S->bh : nullptr;
+    f.eedge = edges(S);
     f.nx = c.nx;
     f.ny = c.ny;
     f.ntx = S->ntx;
@@ -681,22 +675,7 @@ int build_tiles(pic_sim *S, hipStream_t stream)
 
 }  // namespace
 
-namespace {
-// with_side: create pic_step's second stream (the members of a batch have
-// none: the batch forks its own step)
-int init_sim(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream, pic_sim **out, bool with_side);
-}  // namespace
-
 int pic_init(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream, pic_sim **out)
-{
-    return init_sim(cfg, bufs, stream, out, true);
-}
-
-}  // extern "C"
-
-namespace {
-
-int init_sim(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream, pic_sim **out, bool with_side)
 {
     if (!out || !bufs) return PIC_EINVAL;
     *out = nullptr;
@@ -727,6 +706,7 @@ int init_sim(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream,
     S->cacc = (unsigned long long *)(w + L.cacc);
     S->jtile = (float *)(w + L.jtile);
     S->bh = (float *)(w + L.bh);
+    S->eedge = (float *)(w + L.eedge);
     S->rho_prev = (double *)(w + L.rho_prev);
     S->rho_now = (double *)(w + L.rho_now);
     S->jf = cfg->j_filter > 0 ? (float *)(w + L.jf) : nullptr;
@@ -785,25 +765,13 @@ int init_sim(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream,
     if (rc == PIC_OK) rc = hip_ok(hipMemsetAsync(S->err, 0, 64, stream));
     if (rc == PIC_OK) rc = hip_ok(hipMemsetAsync(S->stg_live, 0, sizeof(int), stream));
     if (rc == PIC_OK) rc = build_tiles(S, stream);
-    if (with_side) {
-        // default priority, like every stream of the library's callers
-        if (rc == PIC_OK) rc = hip_ok(hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking));
-        if (rc == PIC_OK) rc = hip_ok(hipEventCreateWithFlags(&S->ev_fork, hipEventDisableTiming));
-        if (rc == PIC_OK) rc = hip_ok(hipEventCreateWithFlags(&S->ev_join, hipEventDisableTiming));
-    }
     if (rc != PIC_OK) {
-        release_side(S);
         delete S;
         return rc;
     }
     *out = S;
     return PIC_OK;
 }
-
-}  // namespace
-
-extern "C" {
-
 
 namespace {
 
@@ -839,22 +807,9 @@ int push_only(pic_sim *S, hipStream_t stream, bool bh)
 // The fold of the tile current halos into J, then the optional filter passes.
 int fold_current(pic_sim *S, hipStream_t stream);
 
-// The field half of a step after a push that formed the first B half step:
-// the J fold (and the filter), then the E step and the second B half step --
-// the fold done by the E step when there is no filter (the same J, bit for
-// bit: both use fold_node).  The same fields as pic_field_advance, bit for
-// bit: the push's half step uses the same per-cell function.
-int field_half(pic_sim *S, hipStream_t stream)
-{
-    const bool fold = S->cfg.j_filter == 0;
-    if (!fold) {
-        const int rc = fold_current(S, stream);
-        if (rc) return rc;
-    }
-    Timed t(S, PIC_KERNEL_FIELD, stream);
-    launch_field_advance(field_args(S, fold, true), S->tile, S->halo, stream);
-    return hip_ok(hipGetLastError());
-}
+// Whether the field half of a step folds J itself (else fold_current has,
+// for the filter): the same J, bit for bit, both use fold_node.
+bool fold_in_field(const pic_sim *S) { return S->cfg.j_filter == 0; }
 
 int fold_current(pic_sim *S, hipStream_t stream)
 {
@@ -866,6 +821,16 @@ int fold_current(pic_sim *S, hipStream_t stream)
         Timed t(S, PIC_KERNEL_FILTER, stream);
         launch_filter(filter_args(S, p), false, stream);
     }
+    return hip_ok(hipGetLastError());
+}
+
+// The field half of a step after a push that formed the first B half step:
+// the E step and the second B half step, the same fields as
+// pic_field_advance, bit for bit (the same per-cell functions).
+int field_half(pic_sim *S, hipStream_t stream)
+{
+    Timed t(S, PIC_KERNEL_FIELD, stream);
+    launch_field_half(field_args(S, fold_in_field(S), true), S->tile, S->halo, stream);
     return hip_ok(hipGetLastError());
 }
 
@@ -956,7 +921,7 @@ int pic_field_advance(pic_sim *S, hipStream_t stream)
 {
     if (!S) return PIC_EINVAL;
     Timed t(S, PIC_KERNEL_FIELD, stream);
-    launch_field_advance(field_args(S, false, false), S->tile, S->halo, stream);
+    launch_field_advance(field_args(S, false, false), stream);
     return hip_ok(hipGetLastError());
 }
 
@@ -1085,28 +1050,26 @@ int pic_step(pic_sim *S, hipStream_t stream)
     if (!S) return PIC_EINVAL;
     int rc = push_only(S, stream, true);
     if (rc) return rc;
-    // Unforked: no sort this step, or no second stream
-    if (S->since_sort < S->cadence || !S->side) {
-        if (S->since_sort >= S->cadence) rc = sort_after_push(S, stream, true);
+    if (!fold_in_field(S)) {
+        rc = fold_current(S, stream);
+        if (rc) return rc;
+    }
+    const bool sort = S->since_sort >= S->cadence;
+    const unsigned split = (1u << PIC_KERNEL_SORT_PLAN) | (1u << PIC_KERNEL_FIELD);
+    if (!sort || (S->cfg.flags & PIC_FLAG_MOTION_SORT) || (S->timing && (S->timing_mask & split))) {
+        // the field half on its own (also when the two are to be timed apart)
+        if (sort) rc = sort_after_push(S, stream, true);
         if (rc == PIC_OK) rc = field_half(S, stream);
         return rc;
     }
-    // Once the push is done, the sort (particles, count records, leaver
-    // lists) and the field half (tile current halos, J, E, B) touch disjoint
-    // data: the field half runs on the second stream, beside the sort, and
-    // the caller's stream waits for it before anything later.  Both halves
-    // are small, latency-bound kernels, so they overlap well.
-    rc = hip_ok(hipEventRecord(S->ev_fork, stream));
-    if (rc) return rc;
-    rc = hip_ok(hipStreamWaitEvent(S->side, S->ev_fork, 0));
-    if (rc) return rc;
-    int rf = field_half(S, S->side);
-    const int rj = hip_ok(hipEventRecord(S->ev_join, S->side));
-    rc = sort_after_push(S, stream, true);
-    // the join is enqueued whatever happened above, so the caller's stream
-    // never runs ahead of work already on the second stream
-    const int rw = rj == PIC_OK ? hip_ok(hipStreamWaitEvent(stream, S->ev_join, 0)) : rj;
-    return rc ? rc : (rf ? rf : rw);
+    S->since_sort = 0;
+    const SortArgs a = sort_args(S, true);
+    {
+        Timed t(S, PIC_KERNEL_SORT_SCAN, stream);
+        launch_sort_scan(a, S->n_tiles, false, stream);
+    }
+    launch_plan_and_field(a, S->n_tiles, field_args(S, fold_in_field(S), true), S->tile, S->halo, stream);
+    return hip_ok(hipGetLastError());
 }
 
 int pic_check(pic_sim *S, hipStream_t stream)
@@ -1322,7 +1285,6 @@ void pic_destroy(pic_sim *S)
             S->pool.push_back(pr.second);
         }
     for (hipEvent_t e : S->pool) (void)hipEventDestroy(e);
-    release_side(S);
     delete S;
 }
 
@@ -1347,22 +1309,19 @@ struct pic_batch {
     FieldArgs *d_field;
     FilterArgs *d_filter;   // 2 n: the even passes, then the odd passes
     int j_filter;
-    int4 *push_items, *node_items, *count_items, *scan_items, *plan_items;
-    int n_push, n_node, n_count, n_scan, n_plan;
+    int4 *push_items, *node_items, *region_items, *count_items, *scan_items, *plan_items;
+    int n_push, n_node, n_region, n_count, n_scan, n_plan;
     int max_blocks;   // the most scan blocks of one member
     hipGraph_t graph;
     hipGraphExec_t exec;
-    // the field half of a sorting step runs here beside the sort (as in pic_step)
-    hipStream_t side;
-    hipEvent_t ev_fork, ev_join;
 };
 
 namespace {
 
 struct BatchLayout {
-    size_t d_push, d_jr, d_sort, d_field, d_filter, push_items, node_items, count_items, scan_items, plan_items,
-        total;
-    int n_push, n_node, n_count, n_scan, n_plan;
+    size_t d_push, d_jr, d_sort, d_field, d_filter, push_items, node_items, region_items, count_items, scan_items,
+        plan_items, total;
+    int n_push, n_node, n_region, n_count, n_scan, n_plan;
 };
 
 int batch_validate(int n, const pic_config *cfgs)
@@ -1383,12 +1342,13 @@ int batch_validate(int n, const pic_config *cfgs)
 BatchLayout batch_layout(int n, const pic_config *cfgs)
 {
     BatchLayout L;
-    L.n_push = L.n_node = L.n_count = L.n_scan = L.n_plan = 0;
+    L.n_push = L.n_node = L.n_region = L.n_count = L.n_scan = L.n_plan = 0;
     for (int i = 0; i < n; ++i) {
         const pic_config &c = cfgs[i];
         const int nt = (c.nx / c.tile) * (c.ny / c.tile);
         L.n_push += nt;
         L.n_node += ((c.nx + 63) / 64) * ((c.ny + 3) / 4);
+        L.n_region += eb_cols(c.nx) * eb_rows(c.ny);
         L.n_count += c.n_species * ((nt + kScanBlock - 1) / kScanBlock);
         L.n_scan += c.n_species;
         L.n_plan += c.n_species * ((nt + kSortWaves - 1) / kSortWaves);
@@ -1406,11 +1366,26 @@ BatchLayout batch_layout(int n, const pic_config *cfgs)
     L.d_filter = take(2 * n * sizeof(FilterArgs));
     L.push_items = take(L.n_push * sizeof(int4));
     L.node_items = take(L.n_node * sizeof(int4));
+    L.region_items = take(L.n_region * sizeof(int4));
     L.count_items = take(L.n_count * sizeof(int4));
     L.scan_items = take(L.n_scan * sizeof(int4));
     L.plan_items = take(L.n_plan * sizeof(int4));
     L.total = p;
     return L;
+}
+
+SortBatch sort_batch(const pic_batch *b)
+{
+    SortBatch sb;
+    sb.descs = b->d_sort;
+    sb.count_items = b->count_items;
+    sb.n_count = b->n_count;
+    sb.scan_items = b->scan_items;
+    sb.n_scan = b->n_scan;
+    sb.plan_items = b->plan_items;
+    sb.n_plan = b->n_plan;
+    sb.max_blocks = b->max_blocks;
+    return sb;
 }
 
 // One step of every member; the sort only when `sort` is set (the last step
@@ -1423,34 +1398,23 @@ void batch_enqueue_step(pic_batch *b, bool sort, bool rebase, hipStream_t stream
         launch_push_batch(b->tile, b->replicas, b->jm, b->dm, b->halo, b->ppl, b->d_push, b->push_items,
                           b->n_push, rebase, stream);
     }
-    // with a sort, the field half goes to the second stream (disjoint data)
-    const bool fork = sort && b->side;
-    hipStream_t fs = stream;
-    if (fork) {
-        (void)hipEventRecord(b->ev_fork, stream);
-        (void)hipStreamWaitEvent(b->side, b->ev_fork, 0);
-        fs = b->side;
-    }
-    // the J fold, fused into the field advance when there is no filter
-    if (b->j_filter > 0) {
-        launch_j_reduce_batch(b->tile, b->halo, b->d_jr, b->node_items, b->n_node, fs);
+    // J folded and filtered, or folded by the field half when there is no filter
+    const bool fold = b->j_filter == 0;
+    if (!fold) {
+        launch_j_reduce_batch(b->tile, b->halo, b->d_jr, b->node_items, b->n_node, stream);
         for (int p = 0; p < b->j_filter; ++p)
-            launch_filter_batch(b->d_filter + (p & 1) * b->sims.size(), b->node_items, b->n_node, fs);
+            launch_filter_batch(b->d_filter + (p & 1) * b->sims.size(), b->node_items, b->n_node, stream);
     }
-    launch_field_advance_batch(b->d_field, b->node_items, b->n_node, b->j_filter == 0, true, b->tile, b->halo,
-                               fs);
-    if (fork) (void)hipEventRecord(b->ev_join, b->side);
-    SortBatch sb;
-    sb.descs = b->d_sort;
-    sb.count_items = b->count_items;
-    sb.n_count = b->n_count;
-    sb.scan_items = b->scan_items;
-    sb.n_scan = b->n_scan;
-    sb.plan_items = b->plan_items;
-    sb.n_plan = b->n_plan;
-    sb.max_blocks = b->max_blocks;
-    if (sort) launch_sort_batch(sb, (b->sims[0]->cfg.flags & PIC_FLAG_MOTION_SORT) != 0, stream);
-    if (fork) (void)hipStreamWaitEvent(stream, b->ev_join, 0);
+    const SortBatch sb = sort_batch(b);
+    const bool motion = (b->sims[0]->cfg.flags & PIC_FLAG_MOTION_SORT) != 0;
+    if (sort) launch_sort_scan_batch(sb, motion, stream);
+    if (sort && !motion) {
+        // the in-place sort's fill is left to the next push
+        launch_plan_and_field_batch(sb, b->d_field, b->region_items, b->n_region, fold, b->tile, b->halo, stream);
+        return;
+    }
+    if (sort) launch_motion_batch(sb, stream);
+    launch_field_half_batch(b->d_field, b->region_items, b->n_region, fold, b->tile, b->halo, stream);
 }
 
 }  // namespace
@@ -1478,16 +1442,9 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
 
     pic_batch *B = new (std::nothrow) pic_batch();
     if (!B) return PIC_EINVAL;
-    rc = hip_ok(hipStreamCreateWithFlags(&B->side, hipStreamNonBlocking));
-    if (rc == PIC_OK) rc = hip_ok(hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming));
-    if (rc == PIC_OK) rc = hip_ok(hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming));
-    if (rc) {
-        pic_batch_destroy(B);
-        return rc;
-    }
     for (int i = 0; i < n; ++i) {
         pic_sim *S = nullptr;
-        rc = init_sim(&cfgs[i], &bufs[i], stream, &S, false);
+        rc = pic_init(&cfgs[i], &bufs[i], stream, &S);
         if (rc) {
             pic_batch_destroy(B);
             return rc;
@@ -1512,11 +1469,13 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
     B->d_filter = (FilterArgs *)(d + L.d_filter);
     B->push_items = (int4 *)(d + L.push_items);
     B->node_items = (int4 *)(d + L.node_items);
+    B->region_items = (int4 *)(d + L.region_items);
     B->count_items = (int4 *)(d + L.count_items);
     B->scan_items = (int4 *)(d + L.scan_items);
     B->plan_items = (int4 *)(d + L.plan_items);
     B->n_push = L.n_push;
     B->n_node = L.n_node;
+    B->n_region = L.n_region;
     B->n_count = L.n_count;
     B->n_scan = L.n_scan;
     B->n_plan = L.n_plan;
@@ -1532,15 +1491,17 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
     std::vector<SortArgs> hs(n);
     std::vector<FieldArgs> hf(n);
     std::vector<FilterArgs> hfl(2 * n);
-    std::vector<int4> push_items, node_items, count_items, scan_items, plan_items;
+    std::vector<int4> push_items, node_items, region_items, count_items, scan_items, plan_items;
     std::vector<std::pair<double, int>> cost(n);
     for (int i = 0; i < n; ++i) {
         const pic_sim *S = B->sims[i];
         hp[i] = push_args(S, true);
+        hp[i].eedge = S->eedge;
         hj[i] = jreduce_args(S);
         hs[i] = sort_args(S, !(S->cfg.flags & PIC_FLAG_MOTION_SORT));
         hs[i].scan = batch_scan_mode(B->max_blocks);
         hf[i] = field_args(S, S->cfg.j_filter == 0, true);
+        hf[i].eedge = S->eedge;
         hfl[i] = filter_args(S, 0);
         hfl[n + i] = filter_args(S, 1);
         int64_t np = 0;
@@ -1548,6 +1509,9 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
         cost[i] = {-(double)np / S->n_tiles, i};   // particles per tile, largest first
         for (int by = 0; by < (S->cfg.ny + 3) / 4; ++by)
             for (int bx = 0; bx < (S->cfg.nx + 63) / 64; ++bx) node_items.push_back(make_int4(i, bx, by, 0));
+        for (int by = 0; by < eb_rows(S->cfg.ny); ++by)
+            for (int bx = 0; bx < eb_cols(S->cfg.nx); ++bx)
+                region_items.push_back(make_int4(i, bx, by, 0));
         for (int s = 0; s < S->cfg.n_species; ++s) {
             for (int k = 0; k < (S->n_tiles + kScanBlock - 1) / kScanBlock; ++k)
                 count_items.push_back(make_int4(i, s, k, 0));
@@ -1570,6 +1534,7 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
     up(B->d_filter, hfl.data(), 2 * n * sizeof(FilterArgs));
     up(B->push_items, push_items.data(), push_items.size() * sizeof(int4));
     up(B->node_items, node_items.data(), node_items.size() * sizeof(int4));
+    up(B->region_items, region_items.data(), region_items.size() * sizeof(int4));
     up(B->count_items, count_items.data(), count_items.size() * sizeof(int4));
     up(B->scan_items, scan_items.data(), scan_items.size() * sizeof(int4));
     up(B->plan_items, plan_items.data(), plan_items.size() * sizeof(int4));
@@ -1636,15 +1601,7 @@ pic_sim *pic_batch_sim(pic_batch *B, int i)
 int pic_batch_sync(pic_batch *B, hipStream_t stream)
 {
     if (!B) return PIC_EINVAL;
-    SortBatch sb;
-    sb.descs = B->d_sort;
-    sb.count_items = B->count_items;
-    sb.n_count = B->n_count;
-    sb.scan_items = B->scan_items;
-    sb.n_scan = B->n_scan;
-    sb.plan_items = B->plan_items;
-    sb.n_plan = B->n_plan;
-    sb.max_blocks = B->max_blocks;
+    const SortBatch sb = sort_batch(B);
     launch_settle_batch(sb, B->phase == 0, stream);   // members without a pending fill have zero fill counts
     return hip_ok(hipGetLastError());
 }
@@ -1666,12 +1623,6 @@ void pic_batch_destroy(pic_batch *B)
     if (B->exec) (void)hipGraphExecDestroy(B->exec);
     if (B->graph) (void)hipGraphDestroy(B->graph);
     for (pic_sim *S : B->sims) pic_destroy(S);
-    if (B->side) {
-        (void)hipStreamSynchronize(B->side);
-        (void)hipStreamDestroy(B->side);
-    }
-    if (B->ev_fork) (void)hipEventDestroy(B->ev_fork);
-    if (B->ev_join) (void)hipEventDestroy(B->ev_join);
     delete B;
 }
 

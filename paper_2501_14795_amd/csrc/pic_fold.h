@@ -8,6 +8,25 @@
 
 namespace pic {
 
+// The compensated sum, per component, of the values of up to four halos in
+// order (absent ones zero, which leaves it unchanged).
+__device__ __forceinline__ void fold_sum(const float v[4][3], float out[3])
+{
+    float sum[3] = {0.0f, 0.0f, 0.0f}, cmp[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float x = v[q][c];
+            const float t = sum[c] + x;
+            const float bp = t - sum[c];
+            cmp[c] += (sum[c] - (t - bp)) + (x - bp);
+            sum[c] = t;
+        }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[c] = sum[c] + cmp[c];
+}
+
 // J at node (gx, gy) = the sum over the tiles whose current halo (relative
 // nodes -H..T+H, (T+2H+1)^2 per component, tile by tile in jtile) covers the
 // node, in fixed (ty, tx) order with compensation.  A node at tile-relative
@@ -43,19 +62,7 @@ __device__ __forceinline__ void fold_node(const float *__restrict__ jtile, int n
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[q][c] = valid ? src[c * JP] : 0.0f;
     }
-    float sum[3] = {0.0f, 0.0f, 0.0f}, cmp[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const float x = v[q][c];
-            const float t = sum[c] + x;
-            const float bp = t - sum[c];
-            cmp[c] += (sum[c] - (t - bp)) + (x - bp);
-            sum[c] = t;
-        }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c] = sum[c] + cmp[c];
+    fold_sum(v, out);
 }
 
 }  // namespace pic

@@ -68,7 +68,9 @@ struct FieldArgs {
     float *fld;           // the nine field planes
     const float *jtile;   // tile current halos folded into J by the E step, or null: J is input
     const float *bh;      // B after the step's first half step, formed by the push (three planes),
-                          // or null: the field advance forms it in place
+                          // and the edge strips of the old E, or null: the field advance forms the
+                          // half step in place
+    const float *eedge;   // null (the grid is large): E and the second B half step as two launches
     int nx, ny, ntx, nty;
     float hdx, hdy;       // (dt/2)/dx, (dt/2)/dy  (B half steps)
     float dt, dtdx, dtdy; // E full step
@@ -114,8 +116,10 @@ struct SortBatch {
 void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s);
 // SortArgs::scan of the members of a batch
 int batch_scan_mode(int max_blocks);
-// motion: the motion-class sort (PIC_FLAG_MOTION_SORT) instead of the in-place one
-void launch_sort_batch(const SortBatch &b, bool motion, hipStream_t s);
+// the recount of every member; offsets: tile_offset too (as launch_sort_scan)
+void launch_sort_scan_batch(const SortBatch &b, bool offsets, hipStream_t s);
+// the motion-class sort after it, copied back
+void launch_motion_batch(const SortBatch &b, hipStream_t s);
 // the motion-class sort after the recount and scan: every particle into the
 // staging arrays at its new slot, then the staging arrays copied back
 void launch_motion_scatter(const SortArgs &a, int n_tiles, hipStream_t s);
@@ -165,13 +169,23 @@ void launch_place_new(const int32_t *src, int32_t *dst, int16_t *ldst, int n, in
                       int *err, hipStream_t s);
 void launch_filter(const FilterArgs &a, bool fp64, hipStream_t s);
 void launch_filter_batch(const FilterArgs *descs, const int4 *items, int n_items, hipStream_t s);
-// the three Yee sub-steps (k_field.hip); with f.jtile set, the E step folds
-// the tile current halos (tiles of edge `tile`, halo pad `halo`) into J
-void launch_field_advance(const FieldArgs &f, int tile, int halo, hipStream_t s);
-// batched: items (simulation, 64 x 4 cell block); fold: every member's
+// the three Yee sub-steps in place (k_field.hip), J read
+void launch_field_advance(const FieldArgs &f, hipStream_t s);
+// one B half step, in place or from f.bh
+void launch_field_b(const FieldArgs &f, hipStream_t s);
+// the field half after a push that formed the first half step (f.bh): E and
+// the second B half step; with f.jtile set, J is folded from the tile current
+// halos (tiles of edge `tile`, halo pad `halo`)
+void launch_field_half(const FieldArgs &f, int tile, int halo, hipStream_t s);
+// batched: items (simulation, block column, block row); fold: every member's
 // FieldArgs has jtile set
-void launch_field_advance_batch(const FieldArgs *descs, const int4 *items, int n_items, bool fold, bool bh, int tile,
-                                int halo, hipStream_t s);
+void launch_field_half_batch(const FieldArgs *descs, const int4 *items, int n_items, bool fold, int tile, int halo,
+                             hipStream_t s);
+// the field half and the in-place sort's plan, which touch disjoint data, in
+// one launch (k_sort.hip)
+void launch_plan_and_field(const SortArgs &a, int n_tiles, const FieldArgs &f, int tile, int halo, hipStream_t s);
+void launch_plan_and_field_batch(const SortBatch &b, const FieldArgs *fields, const int4 *regions, int n_regions,
+                                 bool fold, int tile, int halo, hipStream_t s);
 
 // Projection of E (Eq. 17) or B (Eq. 18) by a direct solve or by conjugate
 // gradients, k_poisson.hip.

@@ -105,7 +105,7 @@ constexpr int push_lds_bytes(int T, int R, int JM, int H = 1)
 {
     return (T + 2 * H) * (T + 2 * H) * (push_packed(T) ? 48 : 24) +
            R * 3 * (T + 2 * H + 1) * (T + 2 * H + 1) * (JM == kJFixed ? 8 : 4) +
-           kMaxSpecies * (9 * push_waves(T) + push_waves(T)) * 4 + push_waves(T) * 6 * kMotionBuf * 4 +
+           kMaxSpecies * (9 * push_waves(T) + push_waves(T) + push_waves(T) + 3) * 4 + push_waves(T) * 6 * kMotionBuf * 4 +
            (push_packed(T) ? push_waves(T) * 7 * kLeaverBuf * 4 : 0) + push_waves(T) * 64 * 4;
 }
 
@@ -146,6 +146,21 @@ __device__ __forceinline__ int tcell_x(int c) { return __builtin_amdgcn_sbfe(c, 
 __device__ __forceinline__ int tcell_y(int c) { return __builtin_amdgcn_sbfe(c, 8, 8); }
 // a particle that left the moving window: (-128, -128), no tile
 constexpr int kTCellRemoved = 0x8080;
+
+// The edge strips: E before a step on every kEdgeX-th column (Ey, Ez) and
+// every kEdgeY-th row (Ex, Ez), kept by the push for the field half, whose
+// blocks need the old E just beyond their region while its owner overwrites
+// it.  Per column 2 ny values, then per row 2 nx.
+constexpr int kEdgeX = 64, kEdgeY = 8;
+__host__ __device__ __forceinline__ int64_t edge_col(int ny, int c, int j) { return (int64_t)c * 2 * ny + j; }
+__host__ __device__ __forceinline__ int64_t edge_row(int nx, int ny, int r, int i)
+{
+    return (int64_t)((nx + kEdgeX - 1) / kEdgeX) * 2 * ny + (int64_t)r * 2 * nx + i;
+}
+__host__ __device__ __forceinline__ int64_t edge_size(int nx, int ny)
+{
+    return edge_row(nx, ny, (ny + kEdgeY - 1) / kEdgeY, 0);
+}
 
 // One species' particles as the kernels stream them: a structure of arrays
 // (n entries each), tile-relative cells.
@@ -216,6 +231,7 @@ struct PushArgs {
     const float *fld;     // Ex Ey Ez Bx By Bz planes
     float *bh;            // or null: B after the first half step of the field advance (three planes,
                           // each tile writes its cells from its staged halo)
+    float *eedge;         // with bh: the edge strips of E (edge_col, edge_row), or null
     float hdx, hdy;       // (dt/2)/dx, (dt/2)/dy
     float *jtile;         // [n_tiles][3][(T+2H+1)^2], physical current of each tile halo
     int *err;
