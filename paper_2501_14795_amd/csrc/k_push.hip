@@ -725,17 +725,16 @@ __device__ __forceinline__ Moved advance(const PushArgs &a, const Chunk &p, bool
     return m;
 }
 
-// One tile of one simulation, by the whole workgroup (push_waves(T) wavefronts).
+// One tile of one simulation, by the whole workgroup (W wavefronts).
 // C: particles per lane per pass of the particle loop (64-particle chunks
 // carried side by side).
-template <int T, int R, int JM, int DM, int H, int C, bool MS = false>
+template <int T, int R, int JM, int DM, int H, int C, bool MS = false, int W = push_waves(T)>
 __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, const bool rebase)
 {
     static_assert(cadence_ok(T, H), "halo pad not supported for this tile");
     constexpr int NE = T + 2 * H;       // staged E/B cells per axis: relative -H..T+H-1
     constexpr int NJ = T + 2 * H + 1;   // current halo nodes per axis: relative -H..T+H
     constexpr int JP = NJ * NJ;
-    constexpr int W = push_waves(T);   // wavefronts of the workgroup
     constexpr int NT = 64 * W;         // its threads
     using Acc = typename JAcc<JM>::T;
 
@@ -1156,6 +1155,14 @@ __global__ void __launch_bounds__(64 * push_waves(T), (push_waves_per_simd<T, R,
     push_tile<T, R, JM, DM, H, C, MS>(a, blockIdx.x, a.rebase != 0);
 }
 
+// Few tiles (kFewTiles): kFewWaves wavefronts each, four per SIMD.
+template <int T, int JM, int DM, int H, int C>
+__global__ void __launch_bounds__(64 * kFewWaves, kFewWaves / 4) k_push_few(PushArgs a)
+{
+    static_assert(push_lds_bytes(T, 1, JM, H, kFewWaves) <= kLdsBytes, "LDS of one workgroup");
+    push_tile<T, 1, JM, DM, H, C, false, kFewWaves>(a, blockIdx.x, a.rebase != 0);
+}
+
 // Many simulations in one launch: one workgroup per (simulation, tile) item.
 // The items come largest simulations first and the hardware dispatches
 // workgroups in order, so the expensive tiles start early and the cheap ones
@@ -1230,12 +1237,21 @@ struct PushLaunch {
     int n_items;
     int rebase;               // batched: the pushes follow a sort
     int ms;                   // single: the particles may wait in the motion-class sort's staging arrays
+    int waves;                // single: wavefronts per tile, push_waves(T) or kFewWaves
     hipStream_t s;
     template <int T, int R, int JM, int DM, int H, int C>
     void go() const
     {
         if constexpr (push_lds_bytes(T, R, JM, H) <= kLdsBytes && cadence_ok(T, H)) {
             if (single) {
+                // few_tiles_ok: the default chunks per lane, one current copy, fixed point
+                if constexpr (R == 1 && JM == kJFixed && C == (DM == kDepQuad ? 1 : 2)) {
+                    if (waves == kFewWaves) {
+                        hipLaunchKernelGGL((k_push_few<T, JM, DM, H, C>), dim3(n_tiles), dim3(64 * kFewWaves), 0, s,
+                                           *single);
+                        return;
+                    }
+                }
                 // the reading of the staging arrays is built for the default current and deposit
                 if constexpr (R == 1 && JM == kJFixed && DM == kDepVB) {
                     if (ms) {
@@ -1320,16 +1336,16 @@ static void push_t(const PushLaunch &L, int tile, int replicas, int jmode, int d
 }
 
 void launch_push_deposit(int tile, int replicas, int jmode, int dmode, int halo, int ppl, const PushArgs &a,
-                         int n_tiles, bool ms, hipStream_t s)
+                         int n_tiles, bool ms, int waves, hipStream_t s)
 {
-    PushLaunch L{&a, n_tiles, nullptr, nullptr, 0, 0, ms ? 1 : 0, s};
+    PushLaunch L{&a, n_tiles, nullptr, nullptr, 0, 0, ms ? 1 : 0, waves, s};
     push_t(L, tile, replicas, jmode, dmode, halo, ppl);
 }
 
 void launch_push_batch(int tile, int replicas, int jmode, int dmode, int halo, int ppl, const PushArgs *descs,
                        const int4 *items, int n_items, bool rebase, hipStream_t s)
 {
-    PushLaunch L{nullptr, 0, descs, items, n_items, rebase ? 1 : 0, 0, s};
+    PushLaunch L{nullptr, 0, descs, items, n_items, rebase ? 1 : 0, 0, 0, s};
     push_t(L, tile, replicas, jmode, dmode, halo, ppl);
 }
 

@@ -37,14 +37,13 @@ __global__ void __launch_bounds__(256) k_window_records(const int32_t *__restric
 }
 
 // The tiles of the tile column that holds array column `col`, one per
-// workgroup of push_waves(T) wavefronts, each streaming the run of the
+// workgroup of W wavefronts (the push's), each streaming the run of the
 // section the push kernel would give it.  A particle in column `col` leaves
 // (its cell marked kTCellRemoved, direction kDirRemoved); every other
 // particle stays.  The particles are sorted: each lies in its own tile.
-template <int T>
-__global__ void __launch_bounds__(64 * push_waves(T)) k_window_remove(WindowSpecies w, int ntx, int col)
+template <int T, int W>
+__global__ void __launch_bounds__(64 * W) k_window_remove(WindowSpecies w, int ntx, int col)
 {
-    constexpr int W = push_waves(T);
     __shared__ int s_wl[W];
     const int tile = blockIdx.x * ntx + col / T;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -118,20 +117,26 @@ void launch_zero_column(float *fld, int nx, int ny, int col, hipStream_t s)
     hipLaunchKernelGGL(k_zero_column, dim3((ny + 255) / 256), dim3(256), 0, s, fld, nx, ny, col);
 }
 
-void launch_window_remove(int tile, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col, hipStream_t s)
+template <int T>
+static void window_remove(int waves, const WindowSpecies &w, int ntx, int nty, int col, hipStream_t s)
+{
+    if (waves == kFewWaves)
+        hipLaunchKernelGGL((k_window_remove<T, kFewWaves>), dim3(nty), dim3(64 * kFewWaves), 0, s, w, ntx, col);
+    else
+        hipLaunchKernelGGL((k_window_remove<T, push_waves(T)>), dim3(nty), dim3(64 * push_waves(T)), 0, s, w, ntx, col);
+}
+
+void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col,
+                          hipStream_t s)
 {
     if (n_tiles <= 0) return;
     const int64_t entries = (int64_t)n_tiles * kCntStride;
     hipLaunchKernelGGL(k_window_records, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, w.off, w.offp,
                        w.cnt, n_tiles);
     switch (tile) {
-    case 8: hipLaunchKernelGGL((k_window_remove<8>), dim3(nty), dim3(64 * push_waves(8)), 0, s, w, ntx, col); break;
-    case 16:
-        hipLaunchKernelGGL((k_window_remove<16>), dim3(nty), dim3(64 * push_waves(16)), 0, s, w, ntx, col);
-        break;
-    default:
-        hipLaunchKernelGGL((k_window_remove<32>), dim3(nty), dim3(64 * push_waves(32)), 0, s, w, ntx, col);
-        break;
+    case 8: window_remove<8>(waves, w, ntx, nty, col, s); break;
+    case 16: window_remove<16>(waves, w, ntx, nty, col, s); break;
+    default: window_remove<32>(waves, w, ntx, nty, col, s); break;
     }
 }
 

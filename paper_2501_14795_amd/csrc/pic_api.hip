@@ -42,6 +42,16 @@ int cadence_of(const pic_config *c) { return c->sort_every ? c->sort_every : 1; 
 int halo_of(const pic_config *c) { return cadence_of(c) + shape_pad(d_mode(c)); }
 int ppl_of(const pic_config *c) { return c->ppl ? c->ppl : 2; }
 
+// Whether a simulation is pushed by kFewWaves wavefronts per tile: few tiles,
+// and the options that kernel is built for (the motion-class sort pays for its
+// own pass over the particles, not for the push's).
+bool few_tiles_ok(const pic_config *c)
+{
+    return (int64_t)(c->nx / c->tile) * (c->ny / c->tile) <= kFewTiles && j_mode(c) == kJFixed && c->j_replicas <= 1 &&
+           ppl_of(c) == 2 && !(c->flags & PIC_FLAG_MOTION_SORT);
+}
+int waves_of(const pic_config *c) { return few_tiles_ok(c) ? kFewWaves : push_waves(c->tile); }
+
 int default_replicas(const pic_config *c)
 {
     if (j_mode(c) == kJFixed) return 1;   // integer LDS atomics need no replicas
@@ -150,7 +160,7 @@ Layout make_layout(const pic_config *c)
             for (int k = 0; k < 6; ++k) L.stg[s][k] = take(n * (k == 0 ? sizeof(int16_t) : sizeof(float)));
         L.mcount[s] = take((size_t)3 * n_tiles * sizeof(int32_t));   // movers; new counts and their prefix
         L.fcount[s] = take((size_t)n_tiles * sizeof(int32_t));       // pending fill per tile
-        L.fbase[s] = take((size_t)n_tiles * push_waves(T) * sizeof(int32_t));
+        L.fbase[s] = take((size_t)n_tiles * waves_of(c) * sizeof(int32_t));
         L.bsum[s] = take((size_t)(n_tiles / kScanBlock + 1) * sizeof(int32_t));
     }
     L.total = p;
@@ -163,6 +173,7 @@ struct pic_sim {
     pic_config cfg;
     pic_buffers buf;
     int ntx, nty, n_tiles, tile, replicas;
+    int waves;          // the push's wavefronts per tile
     char *work;
     int *err;
     int *stg_live;      // nonzero: the particles wait in the motion-class sort's staging arrays
@@ -516,7 +527,7 @@ SortArgs sort_args(const pic_sim *S, bool defer = false)
     a.ntx = S->ntx;
     a.nty = S->nty;
     a.tile = S->tile;
-    a.waves = push_waves(S->tile);
+    a.waves = S->waves;
     a.n_tiles = S->n_tiles;
     a.n_species = c.n_species;
     for (int s = 0; s < c.n_species; ++s) {
@@ -697,6 +708,7 @@ int pic_init(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream,
     S->ntx = cfg->nx / cfg->tile;
     S->nty = cfg->ny / cfg->tile;
     S->n_tiles = S->ntx * S->nty;
+    S->waves = waves_of(cfg);
     S->replicas = cfg->j_replicas ? cfg->j_replicas : default_replicas(cfg);
     char *w = (char *)bufs->work;
     S->work = w;
@@ -795,7 +807,7 @@ int push_only(pic_sim *S, hipStream_t stream, bool bh)
     {
         Timed t(S, PIC_KERNEL_PUSH, stream);
         launch_push_deposit(S->tile, S->replicas, j_mode(&S->cfg), d_mode(&S->cfg), S->halo, ppl_of(&S->cfg), a,
-                            S->n_tiles, ms, stream);
+                            S->n_tiles, ms, S->waves, stream);
     }
     // the push has taken the particles from wherever they were: from now on
     // the particle arrays hold them
@@ -982,7 +994,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
         ws.cnt = P.cnt;
         ws.leav = P.leav;
         ws.removed = S->wrem + s;
-        launch_window_remove(S->tile, ws, S->ntx, S->nty, S->n_tiles, col, stream);
+        launch_window_remove(S->tile, S->waves, ws, S->ntx, S->nty, S->n_tiles, col, stream);
         a.sp[s].removed = S->wrem + s;
     }
     if (rc == PIC_OK) rc = hip_ok(hipGetLastError());
@@ -1449,6 +1461,7 @@ int pic_batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, void 
             pic_batch_destroy(B);
             return rc;
         }
+        S->waves = push_waves(S->tile);   // the batch's push: its tiles fill the device together
         B->sims.push_back(S);
     }
     B->tile = cfgs[0].tile;

@@ -81,8 +81,9 @@ struct FieldArgs {
 // ppl: particles per lane per pass of the push loop (1, 2 or 4; ppl_ok)
 // ms: the particles may wait in the motion-class sort's staging arrays
 // (PushArgs::stg_live decides on the device; the default current and deposit only)
+// waves: wavefronts per tile, push_waves(tile) or kFewWaves (few_tiles_ok)
 void launch_push_deposit(int tile, int replicas, int jmode, int dmode, int halo, int ppl, const PushArgs &a,
-                         int n_tiles, bool ms, hipStream_t s);
+                         int n_tiles, bool ms, int waves, hipStream_t s);
 void launch_j_reduce(int tile, int halo, const JReduceArgs &r, hipStream_t s);
 // rebase: the pushes follow a sort (PushArgs::rebase of every member)
 void launch_push_batch(int tile, int replicas, int jmode, int dmode, int halo, int ppl, const PushArgs *descs,
@@ -162,7 +163,9 @@ struct WindowSpecies {
     uint32_t *leav;
     int32_t *removed;   // device count of the particles that left
 };
-void launch_window_remove(int tile, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col, hipStream_t s);
+// waves: the push's wavefronts per tile
+void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col,
+                          hipStream_t s);
 // new particles given in window column nx - 1 into array column col (checked):
 // whole-grid cells to dst, and cells relative to their tiles (of edge tile) to ldst
 void launch_place_new(const int32_t *src, int32_t *dst, int16_t *ldst, int n, int nx, int ny, int col, int tile,

@@ -38,13 +38,21 @@ constexpr int kScanBlock = 256;      // tiles per block of the tile-count scan
 // motion queues) let two workgroups share a compute unit, so one tile's
 // staging and write-out overlap the other's particle stream.
 __host__ __device__ constexpr int push_waves(int T) { return T >= 32 ? 8 : 4; }
+// A simulation with at most kFewTiles tiles, a workgroup per compute unit or
+// fewer, is pushed by kFewWaves wavefronts per tile instead: the particle loop is
+// then a chain of dependent passes on a mostly empty device, and four times
+// the wavefronts make it a fourth as long.  Results do not depend on it.
+// (16 tiles of 16 x 16 with 4,096 particles each: push 26 us with four
+// wavefronts, 18 with sixteen; 143 tiles of 6,400: 35 and 24 us.)
+constexpr int kFewTiles = 256;
+constexpr int kFewWaves = 16;
 // LDS layout of the push kernel.  Up to 16 x 16 tiles, where LDS is plentiful:
 // each E/B entry holds its cell and the next one in x (one 16-byte read per
 // stencil row of two components), and leavers are buffered per wavefront and
 // written out as whole lines.  32 x 32 tiles: one cell per entry and leaver
 // copies straight from registers, which is what lets two workgroups share a CU.
 __host__ __device__ constexpr bool push_packed(int T) { return T < 32; }
-constexpr int kMaxWaves = 16;
+constexpr int kMaxWaves = kFewWaves;
 
 // Count record of one tile, written by the push kernel:
 //   [0..8]        particles per direction of motion d = (dty+1)*3 + (dtx+1);
@@ -101,12 +109,13 @@ static_assert(kMotionBuf >= 64 && kLeaverBuf >= 64, "per-wavefront LDS buffers m
 // halo pad H (the sort cadence: between two sorts a particle may stray up to
 // H - 1 cells outside its tile, so the E/B halo holds cells -H..T+H-1 and
 // the current halo nodes -H..T+H).
-constexpr int push_lds_bytes(int T, int R, int JM, int H = 1)
+constexpr int push_lds_bytes(int T, int R, int JM, int H = 1, int W = 0)
 {
+    if (W == 0) W = push_waves(T);
     return (T + 2 * H) * (T + 2 * H) * (push_packed(T) ? 48 : 24) +
            R * 3 * (T + 2 * H + 1) * (T + 2 * H + 1) * (JM == kJFixed ? 8 : 4) +
-           kMaxSpecies * (9 * push_waves(T) + push_waves(T) + push_waves(T) + 3) * 4 + push_waves(T) * 6 * kMotionBuf * 4 +
-           (push_packed(T) ? push_waves(T) * 7 * kLeaverBuf * 4 : 0) + push_waves(T) * 64 * 4;
+           kMaxSpecies * (9 * W + W + W + 3) * 4 + W * 6 * kMotionBuf * 4 +
+           (push_packed(T) ? W * 7 * kLeaverBuf * 4 : 0) + W * 64 * 4;
 }
 
 // Sort cadences the push kernel is built for: every 1, 2 or 4 steps, with
