@@ -12,28 +12,17 @@
 
 namespace pic {
 
-// E and B (planes 0..5) of array column `col` become zero
-__global__ void __launch_bounds__(256) k_zero_column(float *__restrict__ fld, int nx, int ny, int col)
+// E and B (planes 0..5) of array column `col` become zero, and the counts of
+// the particles that left.
+__global__ void __launch_bounds__(256) k_zero_column(float *__restrict__ fld, int nx, int ny, int col,
+                                                     int32_t *__restrict__ removed)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < kMaxSpecies) removed[j] = 0;
     if (j >= ny) return;
     const int64_t P = (int64_t)nx * ny;
     const int64_t k = (int64_t)j * nx + col;
     for (int c = 0; c < 6; ++c) fld[c * P + k] = 0.0f;
-}
-
-// Count records of a step in which nothing moves: all particles of a tile
-// stay (direction 4), no leavers.  One thread per record entry; and the copy
-// of the old sections for the sort.
-__global__ void __launch_bounds__(256) k_window_records(const int32_t *__restrict__ off, int32_t *__restrict__ offp,
-                                                        int32_t *__restrict__ cnt, int n_tiles)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)n_tiles * kCntStride) return;
-    const int t = (int)(i / kCntStride), k = (int)(i % kCntStride);
-    cnt[i] = k == 4 ? off[t + 1] - off[t] : 0;
-    if (k == 0) offp[t] = off[t];
-    if (i == 0) offp[n_tiles] = off[n_tiles];
 }
 
 // The tiles of the tile column that holds array column `col`, one per
@@ -41,10 +30,24 @@ __global__ void __launch_bounds__(256) k_window_records(const int32_t *__restric
 // section the push kernel would give it.  A particle in column `col` leaves
 // (its cell marked kTCellRemoved, direction kDirRemoved); every other
 // particle stays.  The particles are sorted: each lies in its own tile.
+//
+// The blocks after those write the count records of all other tiles, in
+// which nothing moves (all particles stay, direction 4), one thread per entry,
+// and the copy of the old sections for the sort.
 template <int T, int W>
-__global__ void __launch_bounds__(64 * W) k_window_remove(WindowSpecies w, int ntx, int col)
+__global__ void __launch_bounds__(64 * W) k_window_remove(WindowSpecies w, int ntx, int nty, int col)
 {
     __shared__ int s_wl[W];
+    if ((int)blockIdx.x >= nty) {
+        const int64_t e = (int64_t)(blockIdx.x - nty) * (64 * W) + threadIdx.x;
+        const int n_tiles = ntx * nty;
+        if (e >= (int64_t)n_tiles * kCntStride) return;
+        const int t = (int)(e / kCntStride), k = (int)(e % kCntStride);
+        if (t % ntx != col / T) w.cnt[e] = k == 4 ? w.off[t + 1] - w.off[t] : 0;
+        if (k == 0) w.offp[t] = w.off[t];
+        if (e == 0) w.offp[n_tiles] = w.off[n_tiles];
+        return;
+    }
     const int tile = blockIdx.x * ntx + col / T;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int begin = w.off[tile], end = w.off[tile + 1];
@@ -83,56 +86,50 @@ __global__ void __launch_bounds__(64 * W) k_window_remove(WindowSpecies w, int n
 }
 
 // The new particles, given in window column nx - 1, into array column `col`:
-// dst[i] = col | iy << 16 and, relative to their tile, ldst[i].  Anything
-// else sets kErrOrder (and is written clamped into the grid, so later kernels
-// of the same call stay in bounds).
-__global__ void __launch_bounds__(256) k_place_new(const int32_t *__restrict__ src, int32_t *__restrict__ dst,
-                                                   int16_t *__restrict__ ldst, int n, int nx, int ny, int col,
-                                                   int tile, int *err)
+// dst.cell[i] = col | iy << 16 and, relative to their tile, ldst[i]; the other
+// arrays as they are.  A cell elsewhere sets kErrOrder (and is written clamped
+// into the grid, so later kernels of the same call stay in bounds).
+__global__ void __launch_bounds__(256) k_place_new(GParts src, GParts dst, int16_t *__restrict__ ldst, int n, int nx,
+                                                   int ny, int col, int tile, int *err)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int c = src[i];
+    const int c = src.cell[i];
     const int ix = c & 0xffff, iy = c >> 16;
     const bool ok = c >= 0 && ix == nx - 1 && iy < ny;
     if (!ok) atomicOr(err, kErrOrder);
     const int jy = ok ? iy : 0;
-    dst[i] = col | (jy << 16);
+    dst.cell[i] = col | (jy << 16);
     ldst[i] = (int16_t)tcell_pack(col & (tile - 1), jy & (tile - 1));
+    dst.x[i] = src.x[i];
+    dst.y[i] = src.y[i];
+    dst.ux[i] = src.ux[i];
+    dst.uy[i] = src.uy[i];
+    dst.uz[i] = src.uz[i];
 }
 
-__global__ void __launch_bounds__(256) k_zero_i32(int32_t *__restrict__ p, int n)
+void launch_zero_column(float *fld, int nx, int ny, int col, int32_t *removed, hipStream_t s)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    hipLaunchKernelGGL(k_zero_column, dim3((ny + 255) / 256), dim3(256), 0, s, fld, nx, ny, col, removed);
 }
 
-void launch_zero_i32(int32_t *p, int n, hipStream_t s)
+template <int T, int W>
+static void window_remove_w(const WindowSpecies &w, int ntx, int nty, int col, hipStream_t s)
 {
-    if (n > 0) hipLaunchKernelGGL(k_zero_i32, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
-}
-
-void launch_zero_column(float *fld, int nx, int ny, int col, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zero_column, dim3((ny + 255) / 256), dim3(256), 0, s, fld, nx, ny, col);
+    const int64_t entries = (int64_t)ntx * nty * kCntStride;
+    hipLaunchKernelGGL((k_window_remove<T, W>), dim3(nty + (unsigned)((entries + 64 * W - 1) / (64 * W))), dim3(64 * W),
+                       0, s, w, ntx, nty, col);
 }
 
 template <int T>
 static void window_remove(int waves, const WindowSpecies &w, int ntx, int nty, int col, hipStream_t s)
 {
-    if (waves == kFewWaves)
-        hipLaunchKernelGGL((k_window_remove<T, kFewWaves>), dim3(nty), dim3(64 * kFewWaves), 0, s, w, ntx, col);
-    else
-        hipLaunchKernelGGL((k_window_remove<T, push_waves(T)>), dim3(nty), dim3(64 * push_waves(T)), 0, s, w, ntx, col);
+    if (waves == kFewWaves) window_remove_w<T, kFewWaves>(w, ntx, nty, col, s);
+    else window_remove_w<T, push_waves(T)>(w, ntx, nty, col, s);
 }
 
-void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col,
-                          hipStream_t s)
+void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int col, hipStream_t s)
 {
-    if (n_tiles <= 0) return;
-    const int64_t entries = (int64_t)n_tiles * kCntStride;
-    hipLaunchKernelGGL(k_window_records, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, w.off, w.offp,
-                       w.cnt, n_tiles);
     switch (tile) {
     case 8: window_remove<8>(waves, w, ntx, nty, col, s); break;
     case 16: window_remove<16>(waves, w, ntx, nty, col, s); break;
@@ -140,7 +137,7 @@ void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, 
     }
 }
 
-void launch_place_new(const int32_t *src, int32_t *dst, int16_t *ldst, int n, int nx, int ny, int col, int tile,
+void launch_place_new(const GParts &src, const GParts &dst, int16_t *ldst, int n, int nx, int ny, int col, int tile,
                       int *err, hipStream_t s)
 {
     if (n > 0)

@@ -965,14 +965,11 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
         if (k[s] == 0) continue;
         const pic_particles &p = S->buf.sp[s];
         auto &P = S->sp[s];
-        const size_t n0 = (size_t)c.species[s].n, bytes = (size_t)k[s] * 4;
+        const size_t n0 = (size_t)c.species[s].n;
         const pic_particles &q = inject[s];
-        void *const dst[5] = {p.x + n0, p.y + n0, p.ux + n0, p.uy + n0, p.uz + n0};
-        const void *const src[5] = {q.x, q.y, q.ux, q.uy, q.uz};
-        for (int f = 0; f < 5 && rc == PIC_OK; ++f)
-            rc = hip_ok(hipMemcpyAsync(dst[f], src[f], bytes, hipMemcpyDeviceToDevice, stream));
-        if (rc) break;
-        launch_place_new(q.cell, p.cell + n0, P.lcell + n0, (int)k[s], c.nx, c.ny, col, c.tile, S->err, stream);
+        launch_place_new(GParts{q.cell, q.x, q.y, q.ux, q.uy, q.uz},
+                         GParts{p.cell + n0, p.x + n0, p.y + n0, p.ux + n0, p.uy + n0, p.uz + n0}, P.lcell + n0,
+                         (int)k[s], c.nx, c.ny, col, c.tile, S->err, stream);
         launch_init_tiles(p.cell + n0, (int32_t)k[s], c.nx, c.ny, c.tile, S->ntx, S->n_tiles, P.inj_off, S->err,
                           stream);
         a.sp[s].inj_off = P.inj_off;
@@ -982,8 +979,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
     if (rc == PIC_OK) rc = read_errors(S, stream);
     if (rc) return rc;
     // 2. E and B of the column that becomes window column nx - 1
-    launch_zero_column(S->buf.fields, c.nx, c.ny, col, stream);
-    launch_zero_i32(S->wrem, kMaxSpecies, stream);
+    launch_zero_column(S->buf.fields, c.nx, c.ny, col, S->wrem, stream);
     // 3. its particles leave: leaver lists and count records for the sort
     for (int s = 0; s < c.n_species && rc == PIC_OK; ++s) {
         auto &P = S->sp[s];
@@ -994,7 +990,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
         ws.cnt = P.cnt;
         ws.leav = P.leav;
         ws.removed = S->wrem + s;
-        launch_window_remove(S->tile, S->waves, ws, S->ntx, S->nty, S->n_tiles, col, stream);
+        launch_window_remove(S->tile, S->waves, ws, S->ntx, S->nty, col, stream);
         a.sp[s].removed = S->wrem + s;
     }
     if (rc == PIC_OK) rc = hip_ok(hipGetLastError());
@@ -1009,9 +1005,7 @@ int pic_move_window(pic_sim *S, const pic_particles *inject, const int64_t *n_in
     for (int s = 0; s < c.n_species && rc == PIC_OK; ++s)
         rc = hip_ok(hipMemcpyAsync(&nn[s], S->sp[s].off + S->n_tiles, sizeof(int32_t), hipMemcpyDeviceToHost,
                                    stream));
-    if (rc == PIC_OK) rc = hip_ok(hipStreamSynchronize(stream));
-    if (rc) return rc;
-    rc = read_errors(S, stream);
+    if (rc == PIC_OK) rc = read_errors(S, stream);   // waits for the counts too
     if (rc) return rc;
     for (int s = 0; s < c.n_species; ++s) c.species[s].n = nn[s];
     S->origin = col + 1 == c.nx ? 0 : col + 1;

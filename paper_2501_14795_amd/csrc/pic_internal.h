@@ -148,10 +148,8 @@ void launch_tile_sort(const TileSortArgs &a, hipStream_t s);
 const uint32_t *launch_tile_sort_perm(const TileSortArgs &a, hipStream_t s);
 void launch_tile_sort_gather(const TileSortArgs &a, const uint32_t *perm, hipStream_t s);
 // moving window (window column i lives in array column (i + origin) mod nx):
-// E and B of array column col become zero
-void launch_zero_column(float *fld, int nx, int ny, int col, hipStream_t s);
-// p[0 .. n) = 0 (a kernel, not a memset node)
-void launch_zero_i32(int32_t *p, int n, hipStream_t s);
+// E and B of array column col and removed[0 .. kMaxSpecies) become zero
+void launch_zero_column(float *fld, int nx, int ny, int col, int32_t *removed, hipStream_t s);
 // the particles of array column col leave; leaver sub-lists and count records
 // of every tile in the push kernel's format (no leaver copies: a removed
 // particle is nobody's mover)
@@ -164,11 +162,11 @@ struct WindowSpecies {
     int32_t *removed;   // device count of the particles that left
 };
 // waves: the push's wavefronts per tile
-void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int n_tiles, int col,
-                          hipStream_t s);
-// new particles given in window column nx - 1 into array column col (checked):
-// whole-grid cells to dst, and cells relative to their tiles (of edge tile) to ldst
-void launch_place_new(const int32_t *src, int32_t *dst, int16_t *ldst, int n, int nx, int ny, int col, int tile,
+void launch_window_remove(int tile, int waves, const WindowSpecies &w, int ntx, int nty, int col, hipStream_t s);
+// n new particles given in window column nx - 1 into array column col (checked):
+// whole-grid cells to dst.cell, and cells relative to their tiles (of edge
+// tile) to ldst
+void launch_place_new(const GParts &src, const GParts &dst, int16_t *ldst, int n, int nx, int ny, int col, int tile,
                       int *err, hipStream_t s);
 void launch_filter(const FilterArgs &a, bool fp64, hipStream_t s);
 void launch_filter_batch(const FilterArgs *descs, const int4 *items, int n_items, hipStream_t s);
