@@ -304,19 +304,17 @@ __device__ __forceinline__ bool tcell_inside(int lc, int T)
 // field half, 2,048 16 x 16 ones (512^2, two beams) 46 -> 26, 64 batched
 // simulations 86 -> 43.
 //
-// NB, candidate iterations per round trip: 6 while every tile's wavefront is
-// resident at once (2048^2 in 32 x 32 tiles: each wavefront's chain of round
-// trips is what counts); 2 for more tiles (a batch's tens of thousands, or
-// small tiles of one large grid), which take several rounds of resident
-// wavefronts, so fewer registers (more wavefronts per SIMD) count more
-constexpr int kPlanBatch = 6;
-constexpr int kPlanBatchB = 2;
-constexpr int kPlanBatchF = 2;   // beside the field half
+// Two candidate iterations per round trip: 48 registers, eight wavefronts per
+// SIMD.  (With the whole leaver lists to read, six were faster while every
+// tile's wavefront was resident at once; with a fourth of the candidates the
+// two forms take the same time: 4,096 tiles 25.2 us each, 2,048 hot ones 73 and
+// 76 event-timed, 16 tiles 15.1 and 12.9.)
+constexpr int kPlanBatch = 2;
 static_assert(kMaxWaves + 14 <= 32, "sort plan lists");
 
-template <int NB = kPlanBatch>
 __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int grp)
 {
+    constexpr int NB = kPlanBatch;
     const int lane = threadIdx.x & 63;
     // one tile per wavefront: the index is wavefront-uniform (scalar registers)
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -617,6 +615,8 @@ __device__ __forceinline__ int motion_class(int lc, int T, int ntx, int nty)
     return far ? 9 : (sty + 1) * 3 + (stx + 1);
 }
 
+constexpr int kTCellNone = 0x10000;   // no particle (cells are 16 bits)
+
 struct Part6 {
     int cell;
     float x, y, ux, uy, uz;
@@ -644,7 +644,9 @@ __device__ __forceinline__ void store_part(const Parts &p, int i, const Part6 &v
 
 // The nt source tiles from tile t0 on, one after the other, each by the whole
 // block: the section's 64-aligned chunks are split into one run per
-// wavefront; a first pass counts every run's particles per class, a second
+// wavefront; a first pass counts every run's particles per class (eight chunks
+// in flight: one at a time it took a fifth of the kernel, 16.8 M particles 185
+// us, now 162, 4.7 TB/s), a second
 // streams the runs again and moves each particle to its slot (its class's
 // first slot in the destination, the class's particles in the earlier runs,
 // its rank in its chunk).  One tile per block for a single simulation (many
@@ -667,13 +669,22 @@ __device__ __forceinline__ void motion_scatter_unit(const SortArgs &a, int spi, 
         wave_range(oA, oB, w, W, lo, hi);
         // pass 1: lane d counts the run's particles of class d
         int mine = 0;
-        for (int c0 = (lo >> 6) << 6; c0 < hi; c0 += 64) {
-            const int i = c0 + lane;
-            const int d = (i >= lo && i < hi) ? motion_class(sp.p.cell[i], T, ntx, nty) : 10;
+        constexpr int U = 8;   // chunks in flight
+        for (int c0 = (lo >> 6) << 6; c0 < hi; c0 += 64 * U) {
+            int lc[U];
 #pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                const int c = __popcll(__ballot(d == k));
-                if (lane == k) mine += c;
+            for (int u = 0; u < U; ++u) {
+                const int i = c0 + 64 * u + lane;
+                lc[u] = i >= lo && i < hi ? gp(sp.p.cell)[i] : kTCellNone;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int d = lc[u] == kTCellNone ? 10 : motion_class(lc[u], T, ntx, nty);
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    const int c = __popcll(__ballot(d == k));
+                    if (lane == k) mine += c;
+                }
             }
         }
         if (lane < 9) s_cls[w][lane] = mine;
@@ -841,8 +852,7 @@ __global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int rebase)
 {
     settle_tile(a, blockIdx.y, blockIdx.x, threadIdx.x, kSettleBlock, rebase != 0);
 }
-template <int NB>
-__global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit<NB>(a, blockIdx.y, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit(a, blockIdx.y, blockIdx.x); }
 
 // The plan and the field half (of a large grid its E step) in one launch: they touch disjoint data, and
 // the plan's wavefronts, which mostly wait, share the chip with the field
@@ -863,7 +873,7 @@ struct PlanMix {
 };
 static PlanMix plan_mix(int n_plan, int n_field) { return PlanMix{n_plan, std::max(1, (n_plan + n_field) / n_plan)}; }
 
-template <int NB, bool FUSED, bool FOLD, int T, int H>
+template <bool FUSED, bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs f, PlanMix mix)
 {
     int q;
@@ -871,7 +881,7 @@ __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs
     if (p >= 0) {
         if (threadIdx.x >= kBlock) return;   // the plan's block is smaller (an ended wavefront holds up no barrier)
         const int groups = mix.n_plan / a.n_species;
-        sort_plan_unit<NB>(a, p / groups, p % groups);
+        sort_plan_unit(a, p / groups, p % groups);
     } else if constexpr (FUSED) {
         const int cols = eb_cols(f.nx);
         field_eb_region<FOLD, T, H>(f, q % cols, q / cols);
@@ -880,7 +890,7 @@ __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs
     }
 }
 
-template <int NB, bool FOLD, int T, int H>
+template <bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd, const int4 *si, const FieldArgs *fd,
                                                          const int4 *fi, PlanMix mix)
 {
@@ -889,7 +899,7 @@ __global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd,
     if (p >= 0) {
         if (threadIdx.x >= kBlock) return;
         const int4 w = si[p];
-        sort_plan_unit<NB>(sd[w.x], w.y, w.z);
+        sort_plan_unit(sd[w.x], w.y, w.z);
     } else {
         const int4 w = fi[q];
         field_eb_region<FOLD, T, H>(fd[w.x], w.y, w.z);
@@ -1009,20 +1019,11 @@ void launch_sort_scan(const SortArgs &a, int n_tiles, bool offsets, hipStream_t 
     else hipLaunchKernelGGL(k_sort_add_base, dim3(nb, a.n_species), dim3(kScanBlock), 0, s, a);
 }
 
-// Plan wavefronts (one per tile and species) that fit the device at once with
-// the six-iteration plan (four wavefronts per SIMD, 256 CUs); beyond, the
-// two-iteration plan runs twice as many at once.
-constexpr int64_t kPlanResident = 4096;
-
 void launch_sort_plan(const SortArgs &args, int n_tiles, hipStream_t s)
 {
     SortArgs a = args;
     a.scan = scan_mode((n_tiles + kScanBlock - 1) / kScanBlock);
-    const dim3 grid((n_tiles + kSortWaves - 1) / kSortWaves, a.n_species);
-    if ((int64_t)n_tiles * a.n_species <= kPlanResident)
-        hipLaunchKernelGGL(k_sort_plan<kPlanBatch>, grid, dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_sort_plan<kPlanBatchB>, grid, dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_sort_plan, dim3((n_tiles + kSortWaves - 1) / kSortWaves, a.n_species), dim3(kBlock), 0, s, a);
 }
 
 void launch_sort_scatter(const SortArgs &a, int n_tiles, hipStream_t s)
@@ -1072,7 +1073,6 @@ void launch_motion_batch(const SortBatch &b, hipStream_t s)
 
 namespace {
 
-template <int NB>
 struct PlanFieldLaunch {
     const SortArgs *a;       // single
     const FieldArgs *f;
@@ -1087,12 +1087,12 @@ struct PlanFieldLaunch {
         const PlanMix mix = plan_mix(n_plan, n_field);
         const dim3 grid(n_plan + n_field);
         if (a && f->eedge) {
-            hipLaunchKernelGGL((k_plan_field<NB, true, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
+            hipLaunchKernelGGL((k_plan_field<true, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
         } else if (a) {   // a large grid: E here, the second B half step after it
-            hipLaunchKernelGGL((k_plan_field<NB, false, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
+            hipLaunchKernelGGL((k_plan_field<false, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
             launch_field_b(*f, s);
         } else
-            hipLaunchKernelGGL((k_plan_field_b<NB, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, b->descs, b->plan_items, fd,
+            hipLaunchKernelGGL((k_plan_field_b<FOLD, T, H>), grid, dim3(kEbThreads), 0, s, b->descs, b->plan_items, fd,
                                fi, mix);
     }
 };
@@ -1105,7 +1105,7 @@ void launch_plan_and_field(const SortArgs &args, int n_tiles, const FieldArgs &f
     a.scan = scan_mode((n_tiles + kScanBlock - 1) / kScanBlock);
     const int n_plan = (n_tiles + kSortWaves - 1) / kSortWaves * a.n_species;
     const int n_field = f.eedge ? eb_cols(f.nx) * eb_rows(f.ny) : e_blocks(f.nx, f.ny);
-    eb_dispatch(PlanFieldLaunch<kPlanBatchF>{&a, &f, n_plan, n_field, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,
+    eb_dispatch(PlanFieldLaunch{&a, &f, n_plan, n_field, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,
                 tile, halo);
 }
 
@@ -1113,7 +1113,7 @@ void launch_plan_and_field_batch(const SortBatch &b, const FieldArgs *fields, co
                                  bool fold, int tile, int halo, hipStream_t s)
 {
     if (b.n_plan == 0) return;
-    eb_dispatch(PlanFieldLaunch<kPlanBatchB>{nullptr, nullptr, b.n_plan, n_regions, &b, fields, regions, s}, fold, tile,
+    eb_dispatch(PlanFieldLaunch{nullptr, nullptr, b.n_plan, n_regions, &b, fields, regions, s}, fold, tile,
                 halo);
 }
 
