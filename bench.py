@@ -8,8 +8,8 @@ seeded, resident in HBM before the timed region.
 
 A timed step is one full PIC step through the C ABI (pic_step): push +
 deposit, then the strict in-place re-sort and the Yee field advance (with the
-fold of the tile currents into J) side by side on two streams, joined before
-the call returns.  `value` counts particle pushes over the whole step.
+fold of the tile currents into J), the sort's plan and the E step in one
+launch.  `value` counts particle pushes over the whole step.
 
 Prints ONE JSON line.  The push kernel's duration comes from HIP events that
 libpic records around it on its launching stream during the timed region;

@@ -10,7 +10,8 @@
 //      two x-neighbours of a stencil row come in one ds_read2;
 //   2. the 64-aligned particle chunks covering the tile's section are split
 //      into contiguous runs, one per wavefront (4 wavefronts per tile up to
-//      16 x 16 tiles, 8 for 32 x 32 tiles, two such workgroups per CU); every chunk is one
+//      16 x 16 tiles, 8 for 32 x 32 tiles, two such workgroups per CU; 16 for a
+//      simulation of few tiles); every chunk is one
 //      coalesced buffer load per SoA array (per-tile buffer base in SGPRs):
 //      the cell as 16 bits relative to the tile, x, y, ux, uy, uz as FP32
 //      (22 bytes a particle), and there is no block barrier in the loop; the
@@ -40,13 +41,14 @@
 //                 slower than integer ones;
 //   4. particles whose tile changed are appended, in slot order, to the
 //      wavefront's leaver sub-list (ballot + mbcnt) with a copy of their new
-//      data, and counted per direction -- the input of the strict sort
-//      (Sec. 4.3, step 1);
+//      data, and counted and listed per direction -- the input of the strict
+//      sort (Sec. 4.3, step 1);
 //   5. the tile's (T+2H+1)^2 current halo is converted to physical units and
-//      written out; k_j_reduce (or the E step of the field advance) then adds
+//      written out; k_j_reduce (or the field half's E step) then adds
 //      the up-to-four overlapping tile halos of every node in a fixed order
 //      with compensation (no global atomics); in pic_step the tile also writes
-//      the first B half step of its own cells from its staged E/B halo.
+//      the first B half step of its own cells from its staged E/B halo, and the
+//      old E on the edge columns and rows the field half works between.
 #include <type_traits>
 
 #include "pic_internal.h"
@@ -1134,7 +1136,8 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                 if (lane == k) taken = __popcll(m);
             }
             at += __shfl(pos, d, 64);
-            if (in) ((PIC_GLOBAL vi2a *)sp.dlist)[(int64_t)begin + at] = vi2a{(int)(v >> 4), e - begin};
+            if (in)
+                ((PIC_GLOBAL vi2a *)sp.dlist)[((int64_t)begin + at) * kListStride] = vi2a{(int)(v >> 4), e - begin};
             pos += taken;
         }
     }

@@ -492,7 +492,7 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
                 if (L >= 1 && L <= W) {
                     v[u] = gp(sp.leav)[at[u]];
                 } else if (m >= 0 && m < 10 && m != rank4 && m != rank4 + 1) {
-                    const vi2a e = ((const PIC_GLOBAL vi2a *)sp.dlist)[at[u]];
+                    const vi2a e = ((const PIC_GLOBAL vi2a *)sp.dlist)[(int64_t)at[u] * kListStride];
                     v[u] = (uint32_t)e.x;
                     rec[u] = (uint32_t)e.y;
                 } else {

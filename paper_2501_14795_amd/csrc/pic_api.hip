@@ -24,7 +24,7 @@ struct Layout {
     size_t wrem = 0, inj_off[kMaxSpecies] = {};
     size_t off[kMaxSpecies][2] = {}, cnt[kMaxSpecies] = {}, leav[kMaxSpecies] = {};
     size_t hole[kMaxSpecies] = {}, stg[kMaxSpecies][6] = {}, mcount[kMaxSpecies] = {}, bsum[kMaxSpecies] = {};
-    size_t lrec[kMaxSpecies] = {}, srec[kMaxSpecies] = {}, dlist[kMaxSpecies] = {}, fcount[kMaxSpecies] = {}, fbase[kMaxSpecies] = {};
+    size_t lrec[kMaxSpecies] = {}, srec[kMaxSpecies] = {}, fcount[kMaxSpecies] = {}, fbase[kMaxSpecies] = {};
     size_t lcell[kMaxSpecies] = {};
     size_t total = 0;
 };
@@ -150,7 +150,6 @@ Layout make_layout(const pic_config *c)
         // leaver records; the full re-sort also borrows the region as six
         // arrays of n values (lp_view)
         L.lrec[s] = take(n * sizeof(LeaverRec) + 6 * kAlign);
-        L.dlist[s] = take(n * sizeof(uint2));   // the leavers by direction
         L.hole[s] = take(n * sizeof(int32_t));
         // mover staging: the in-place sort's 32-byte records (every
         // simulation: the moving window's sort is the in-place one; also the
@@ -160,7 +159,8 @@ Layout make_layout(const pic_config *c)
             for (int k = 0; k < 6; ++k) L.stg[s][k] = take(n * (k == 0 ? sizeof(int16_t) : sizeof(float)));
         L.mcount[s] = take((size_t)3 * n_tiles * sizeof(int32_t));   // movers; new counts and their prefix
         L.fcount[s] = take((size_t)n_tiles * sizeof(int32_t));       // pending fill per tile
-        L.fbase[s] = take((size_t)n_tiles * waves_of(c) * sizeof(int32_t));
+        // (the same whatever the options: room for kFewWaves where there are few tiles)
+        L.fbase[s] = take((size_t)n_tiles * (n_tiles <= kFewTiles ? kFewWaves : push_waves(T)) * sizeof(int32_t));
         L.bsum[s] = take((size_t)(n_tiles / kScanBlock + 1) * sizeof(int32_t));
     }
     L.total = p;
@@ -203,7 +203,7 @@ struct pic_sim {
         Parts stg;         // the motion-class sort's staging (null without PIC_FLAG_MOTION_SORT)
         LeaverRec *srec;   // the in-place sort's mover staging (every simulation)
         LeaverRec *lrec;   // the push's leaver records
-        uint2 *dlist;      // the leavers by direction
+        uint2 *dlist;      // the leavers by direction, in lrec's spare words
         GParts lp;         // the same memory as six arrays of n values (the initial grouping's scratch)
         int32_t *mcount;
         int32_t *fcount;   // holes whose fill a deferred sort left to the next push
@@ -751,7 +751,7 @@ int pic_init(const pic_config *cfg, const pic_buffers *bufs, hipStream_t stream,
         P.stg = motion ? parts_at(L.stg[s]) : Parts{};
         P.srec = (LeaverRec *)(w + L.srec[s]);
         P.lrec = (LeaverRec *)(w + L.lrec[s]);
-        P.dlist = (uint2 *)(w + L.dlist[s]);
+        P.dlist = (uint2 *)P.lrec[0].list;
         {
             size_t o[6];
             const size_t n = (size_t)(cfg->species[s].cap ? cfg->species[s].cap : cfg->species[s].n);

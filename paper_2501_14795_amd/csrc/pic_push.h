@@ -6,6 +6,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "pic.h"
@@ -186,12 +187,16 @@ struct GParts {
 
 // One leaver's new particle data, written by the push and read by the sort:
 // one aligned 32-byte record, so each copy is one memory sector on both sides
-// (six separate arrays would cost six scattered sectors per leaver).
+// (six separate arrays would cost six scattered sectors per leaver).  The two
+// spare words hold an entry of the tile's list of leavers by direction, which
+// has nothing to do with the record beside it (SpeciesDev::dlist).
 struct __attribute__((aligned(32))) LeaverRec {
     int32_t cell;
     float x, y, ux, uy, uz;
-    int32_t pad[2];
+    int32_t list[2];
 };
+constexpr int kListStride = sizeof(LeaverRec) / 8;   // list entries lie this many entries apart
+static_assert(offsetof(LeaverRec, list) == 24 && sizeof(LeaverRec) == 32, "leaver record layout");
 
 // plain clang vectors (HIP's vector classes have no address-space-qualified
 // assignment)
@@ -216,8 +221,9 @@ struct SpeciesDev {
     int32_t *cnt;         // [n_tiles][kCntStride]
     uint32_t *leav;       // [n]: leaver sub-lists, (slot - off[t]) << 4 | direction
     LeaverRec *lrec;      // [n]: the leavers' new particle data, same positions as leav
-    uint2 *dlist;         // [n]: tile t's leavers from off[t] on, by direction of motion, each
-                          // direction in slot order: (slot, position in leav), both relative to off[t];
+    uint2 *dlist;         // [n], kListStride apart (in lrec): tile t's leavers from off[t] on, by
+                          // direction of motion, each direction in slot order: (slot, position in
+                          // leav), both relative to off[t];
                           // null: not wanted (the motion-class sort)
     int32_t *offp;        // a copy of off for the sort, which rewrites off
     // a fill left by the last sort: tile t's fcount[t] holes, slots fhole[off[t] + r]
