@@ -282,7 +282,8 @@ __device__ __forceinline__ bool tcell_inside(int lc, int T)
 // ascending slot order.  W = leaver sub-lists per tile (the push kernel's
 // wavefronts per tile).  Lists:
 //   0             : holes in [A, min(B, oA)), slots of lower old sections
-//                   (hole unless the particle there moved into t)
+//                   (hole unless the particle there moved into t, or is one
+//                   of the window's new particles for t)
 //   1 .. W        : holes among t's W leaver sub-lists, restricted to
 //                   [max(A, oA), min(B, oB))
 //   W + 1         : holes in [max(A, oB), B), slots of higher old sections
@@ -514,7 +515,8 @@ __device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int g
             int slot = at[u];
             const bool in_t = arrived((int)v[u], slot);
             if (L == 0 || L == W + 1) {
-                ph = !in_t;
+                // (a new particle of t appended at a slot of [A, B) stays there)
+                ph = !in_t && !(slot >= i0 && slot < i1);
             } else if (L >= 1 && L <= W) {
                 slot = oA + (int)(v[u] >> 4);
                 ph = slot >= lA && slot < lB;
