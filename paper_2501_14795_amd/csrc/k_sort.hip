@@ -36,6 +36,7 @@
 // whole-grid cells and the 16-bit ones, and the tile offsets of caller
 // particles at initialisation.
 #include "pic_eb.h"
+#include "pic_launch.h"
 
 namespace pic {
 
@@ -803,16 +804,17 @@ __device__ __forceinline__ void fill_unit(const SortArgs &a, int spi, int grp)
     if (lane == 0 && m != 0) sp.fcount[t] = 0;
 }
 
-// One tile for a reader of the particle arrays, by `nt` threads of a block:
-// a fill left pending (as fill_unit), then the whole-grid cells of the tile's
-// section into the caller's cell array from the tile-relative ones (the cell
-// of a particle that has left its tile wraps across the periodic seam).
-// rebase: a sorted state, each cell relative to the tile modulo its edge.
-// All threads of the block take part (a barrier orders the fill's cells
-// before the section's reads); t may be past the last tile.
+// One tile for a reader of the particle arrays, by `nt` threads of a block (a
+// power of two from 16): a fill left pending (as fill_unit), then the
+// whole-grid cells of the tile's section into the caller's cell array from the
+// tile-relative ones (the cell of a particle that has left its tile wraps
+// across the periodic seam).  rebase: a sorted state, each cell relative to the
+// tile modulo its edge.  All threads of the block take part (a barrier orders
+// the fill's cells before the section's reads); t may be past the last tile.
 //
 // Bound by HBM: 6 bytes a particle.  Four slots per thread and pass, from
-// 8-byte groups of the cell array on: one wavefront per tile and one slot
+// 8-byte groups of the cell array on, by as many threads as the tile's
+// particles occupy (settle_threads): one wavefront per tile and one slot
 // per lane, as this was first, left a 32 x 32 tile's 16,384 particles to 256
 // dependent passes.  Fill and cells, before as two launches and now: 16.8 M
 // particles in 1,024 tiles 135 -> 26 us, 67 M in 4,096 tiles 258 -> 121 us
@@ -830,29 +832,40 @@ __device__ __forceinline__ void settle_tile(const SortArgs &a, int spi, int t, i
         const int64_t r = (int64_t)A + k;
         store_parts(sp.p, sp.hole[r], load_leaver(sp.srec, r), gx0, gy0);
     }
-    __syncthreads();
+    if (nt <= 64) {   // within one wavefront: its accesses are in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
     if (tid == 0 && m != 0) sp.fcount[t] = 0;
     const int mask = rebase ? a.tile - 1 : -1;
     auto whole = [&](int lc) {
         return wrap_s(gx0 + (tcell_x(lc) & mask), a.nx) | (wrap_s(gy0 + (tcell_y(lc) & mask), a.ny) << 16);
     };
     for (int64_t i = (int64_t)(A & ~3) + 4 * tid; i < B; i += 4 * nt) {
+        // (a group may reach past the section, and past the last slot into the
+        // padding behind the workspace's 256-byte aligned array; unused there)
+        const vs4 c = *(const PIC_GLOBAL vs4 *)(sp.p.cell + i);
+        const vi4 g{whole(c.x), whole(c.y), whole(c.z), whole(c.w)};
         if (i >= A && i + 4 <= B) {
-            const vs4 c = *(const PIC_GLOBAL vs4 *)(sp.p.cell + i);   // the workspace's array: 256-byte aligned
-            *(PIC_GLOBAL vi4 *)(sp.gcell + i) = vi4{whole(c.x), whole(c.y), whole(c.z), whole(c.w)};
+            *(PIC_GLOBAL vi4 *)(sp.gcell + i) = g;
         } else {   // the section's ends
-            for (int64_t j = i < A ? A : i; j < i + 4 && j < B; ++j) sp.gcell[j] = whole(sp.p.cell[j]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u >= A && i + u < B) gp(sp.gcell)[i + u] = g[u];
         }
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill(SortArgs a) { fill_unit(a, blockIdx.y, blockIdx.x); }
-// one tile per block of kSettleBlock threads: sixteen wavefronts, so a tile
-// of any size has its loads in flight at once also where tiles are few
-constexpr int kSettleBlock = 1024;
-__global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int rebase)
+// 1 << sh threads per tile, as many tiles side by side as the block holds
+constexpr int kSettleBlock = 1024;   // threads per tile, at most
+__global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int sh, int rebase)
 {
-    settle_tile(a, blockIdx.y, blockIdx.x, threadIdx.x, kSettleBlock, rebase != 0);
+    const int q = threadIdx.x >> sh;
+    settle_tile(a, blockIdx.y, blockIdx.x * (blockDim.x >> sh) + q, threadIdx.x & ((1 << sh) - 1), 1 << sh, rebase != 0);
 }
 __global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit(a, blockIdx.y, blockIdx.x); }
 
@@ -938,12 +951,12 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_add_base_b(const SortArgs *
     const int4 w = it[blockIdx.x];
     sort_add_unit(d[w.x], w.y, w.z);
 }
-// the kSortWaves tiles of an item side by side, a quarter of the block each
-__global__ void __launch_bounds__(kSettleBlock) k_settle_b(const SortArgs *d, const int4 *it, int rebase)
+// the kSortWaves tiles of an item side by side, 1 << sh threads each
+__global__ void __launch_bounds__(kSettleBlock) k_settle_b(const SortArgs *d, const int4 *it, int sh, int rebase)
 {
-    constexpr int nt = kSettleBlock / kSortWaves;
     const int4 w = it[blockIdx.x];
-    settle_tile(d[w.x], w.y, w.z * kSortWaves + threadIdx.x / nt, threadIdx.x % nt, nt, rebase != 0);
+    const int q = threadIdx.x >> sh;
+    settle_tile(d[w.x], w.y, w.z * kSortWaves + q, threadIdx.x & ((1 << sh) - 1), 1 << sh, rebase != 0);
 }
 
 __global__ void __launch_bounds__(kBlock) k_motion_scatter_b(const SortArgs *d, const int4 *it)
@@ -1041,14 +1054,20 @@ void launch_fill(const SortArgs &a, int n_tiles, hipStream_t s)
 
 void launch_settle(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_settle, dim3(n_tiles, a.n_species), dim3(kSettleBlock), 0, s, a, rebase ? 1 : 0);
+    int64_t n = 0;
+    for (int k = 0; k < a.n_species; ++k) n = std::max<int64_t>(n, a.sp[k].n);
+    const int nt = settle_threads(n, n_tiles, kSettleBlock);
+    const int block = std::max(nt, kBlock), tiles = block / nt;
+    hipLaunchKernelGGL(k_settle, dim3((n_tiles + tiles - 1) / tiles, a.n_species), dim3(block), 0, s, a,
+                       __builtin_ctz(nt), rebase ? 1 : 0);
 }
 
-void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s)
+void launch_settle_batch(const SortBatch &b, int64_t particles, int64_t sections, bool rebase, hipStream_t s)
 {
-    if (b.n_plan > 0)
-        hipLaunchKernelGGL(k_settle_b, dim3(b.n_plan), dim3(kSettleBlock), 0, s, b.descs, b.plan_items,
-                           rebase ? 1 : 0);
+    if (b.n_plan == 0) return;
+    const int nt = settle_threads(particles, sections, kSettleBlock / kSortWaves);
+    hipLaunchKernelGGL(k_settle_b, dim3(b.n_plan), dim3(nt * kSortWaves), 0, s, b.descs, b.plan_items,
+                       __builtin_ctz(nt), rebase ? 1 : 0);
 }
 
 int batch_scan_mode(int max_blocks) { return max_blocks <= kScanDirect ? kScanSums : kScanBases; }

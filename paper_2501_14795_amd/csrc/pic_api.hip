@@ -1608,8 +1608,12 @@ pic_sim *pic_batch_sim(pic_batch *B, int i)
 int pic_batch_sync(pic_batch *B, hipStream_t stream)
 {
     if (!B) return PIC_EINVAL;
-    const SortBatch sb = sort_batch(B);
-    launch_settle_batch(sb, B->phase == 0, stream);   // members without a pending fill have zero fill counts
+    int64_t particles = 0, sections = 0;
+    for (const pic_sim *S : B->sims) {
+        sections += (int64_t)S->n_tiles * S->cfg.n_species;
+        for (int k = 0; k < S->cfg.n_species; ++k) particles += S->cfg.species[k].n;
+    }
+    launch_settle_batch(sort_batch(B), particles, sections, B->phase == 0, stream);   // members without a pending fill have zero fill counts
     return hip_ok(hipGetLastError());
 }
 

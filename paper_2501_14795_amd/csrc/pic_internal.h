@@ -113,8 +113,8 @@ struct SortBatch {
     const int4 *plan_items; int n_plan;
     int max_blocks;   // the most scan blocks of one member
 };
-// launch_settle for every member
-void launch_settle_batch(const SortBatch &b, bool rebase, hipStream_t s);
+// launch_settle for every member; particles in all their tile sections
+void launch_settle_batch(const SortBatch &b, int64_t particles, int64_t sections, bool rebase, hipStream_t s);
 // SortArgs::scan of the members of a batch
 int batch_scan_mode(int max_blocks);
 // the recount of every member; offsets: tile_offset too (as launch_sort_scan)

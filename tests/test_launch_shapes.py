@@ -1,0 +1,50 @@
+"""Launch shapes (pic_launch.h) over the accepted sizes: a HIP launch has less
+than 2^32 threads on an axis.  The header is plain C++: compiled here with
+g++ and called through ctypes."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2501_14795_amd", "csrc")
+LIMIT = 1 << 32
+
+SOURCE = """
+#include "pic_launch.h"
+extern "C" int settle_threads(int64_t n, int64_t n_tiles, int most) { return pic::settle_threads(n, n_tiles, most); }
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    d = tmp_path_factory.mktemp("shapes")
+    (d / "s.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, str(d / "s.cpp"), "-o",
+                    str(d / "s.so")], check=True)
+    lib = ctypes.CDLL(str(d / "s.so"))
+    lib.settle_threads.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    return lib
+
+
+# the largest accepted grid (32,767 cells an axis) is 4,095^2 tiles of 8 x 8
+TILES = [1, 3, 15, 256, 4096, 65536, 4194304, 8388608, 4095 * 4095]
+PARTICLES = [0, 1, 64, 4095, 1 << 20, (1 << 28) + 1, (1 << 31) - 1]
+
+
+def test_settle_threads(shapes):
+    for tiles in TILES:
+        for n in PARTICLES:
+            nt = shapes.settle_threads(n, tiles, 1024)
+            assert nt in (16, 32, 64, 128, 256, 512, 1024)
+            assert nt == 1024 or 8 * nt * tiles >= n      # two passes of four per thread
+            assert nt == 16 or 4 * nt * tiles < n         # and half as many would not do
+            block = max(nt, 256)
+            assert -(-tiles // (block // nt)) * block < LIMIT, (tiles, n)
+            # a batch: four tiles per block, at most as many sections as its push has workgroups
+            nt = shapes.settle_threads(n, tiles, 256)
+            assert nt <= 256 and -(-tiles // 4) * 4 * nt < LIMIT, (tiles, n)
