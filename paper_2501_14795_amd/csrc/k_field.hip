@@ -70,9 +70,11 @@ __global__ void __launch_bounds__(kEbThreads) k_field_e(FieldArgs a)
 
 // many simulations: items = (simulation, rx, ry)
 template <bool FOLD, int T, int H>
-__global__ void __launch_bounds__(kEbThreads) k_field_half_b(const FieldArgs *d, const int4 *it)
+__global__ void __launch_bounds__(kEbThreads) k_field_half_b(const FieldArgs *d, const int4 *it, int n)
 {
-    const int4 w = it[blockIdx.x];
+    const int b = linear_block();
+    if (b >= n) return;
+    const int4 w = it[b];
     field_eb_region<FOLD, T, H>(d[w.x], w.y, w.z);
 }
 
@@ -99,8 +101,11 @@ struct FieldLaunch {
         } else if (single)
             hipLaunchKernelGGL((k_field_half<FOLD, T, H>), dim3(eb_cols(single->nx), eb_rows(single->ny)),
                                dim3(kEbThreads), 0, s, *single);
-        else if (n_items > 0)
-            hipLaunchKernelGGL((k_field_half_b<FOLD, T, H>), dim3(n_items), dim3(kEbThreads), 0, s, descs, items);
+        else if (n_items > 0) {
+            const BlockGrid g = block_grid(n_items, kEbThreads);
+            hipLaunchKernelGGL((k_field_half_b<FOLD, T, H>), dim3(g.x, g.y), dim3(kEbThreads), 0, s, descs, items,
+                               n_items);
+        }
     }
 };
 

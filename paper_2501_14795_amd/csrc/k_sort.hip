@@ -36,7 +36,6 @@
 // whole-grid cells and the 16-bit ones, and the tile offsets of caller
 // particles at initialisation.
 #include "pic_eb.h"
-#include "pic_launch.h"
 
 namespace pic {
 
@@ -876,7 +875,7 @@ __global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_un
 // launches and two event waits: a 64 x 64 step 53 us, now 38; a 512^2 two-beam
 // step 383, now 366.)
 struct PlanMix {
-    int n_plan, every;
+    int n, n_plan, every;   // blocks, plan blocks
     // the block's plan index, or -1 and its field index in `field`
     __device__ __forceinline__ int plan_of(int b, int &field) const
     {
@@ -886,13 +885,18 @@ struct PlanMix {
         return -1;
     }
 };
-static PlanMix plan_mix(int n_plan, int n_field) { return PlanMix{n_plan, std::max(1, (n_plan + n_field) / n_plan)}; }
+static PlanMix plan_mix(int n_plan, int n_field)
+{
+    return PlanMix{n_plan + n_field, n_plan, std::max(1, (n_plan + n_field) / n_plan)};
+}
 
 template <bool FUSED, bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs f, PlanMix mix)
 {
     int q;
-    const int p = mix.plan_of(blockIdx.x, q);
+    const int b = linear_block();
+    if (b >= mix.n) return;
+    const int p = mix.plan_of(b, q);
     if (p >= 0) {
         if (threadIdx.x >= kBlock) return;   // the plan's block is smaller (an ended wavefront holds up no barrier)
         const int groups = mix.n_plan / a.n_species;
@@ -910,7 +914,9 @@ __global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd,
                                                          const int4 *fi, PlanMix mix)
 {
     int q;
-    const int p = mix.plan_of(blockIdx.x, q);
+    const int b = linear_block();
+    if (b >= mix.n) return;
+    const int p = mix.plan_of(b, q);
     if (p >= 0) {
         if (threadIdx.x >= kBlock) return;
         const int4 w = si[p];
@@ -1106,7 +1112,8 @@ struct PlanFieldLaunch {
     void run() const
     {
         const PlanMix mix = plan_mix(n_plan, n_field);
-        const dim3 grid(n_plan + n_field);
+        const BlockGrid g = block_grid(mix.n, kEbThreads);
+        const dim3 grid(g.x, g.y);
         if (a && f->eedge) {
             hipLaunchKernelGGL((k_plan_field<true, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
         } else if (a) {   // a large grid: E here, the second B half step after it

@@ -6,6 +6,7 @@
 
 #include "pic_internal.h"
 #include "pic_fold.h"
+#include "pic_launch.h"
 #include "pic_yee.h"
 
 namespace pic {
@@ -144,6 +145,9 @@ __device__ __forceinline__ void field_e_block(const FieldArgs &a, int q)
     }
 }
 inline int e_blocks(int nx, int ny) { return (int)(((int64_t)nx * ny + kEbThreads - 1) / kEbThreads); }
+
+// the block's index in a block_grid
+__device__ __forceinline__ int linear_block() { return (int)(blockIdx.x + gridDim.x * blockIdx.y); }
 
 // regions per axis
 __host__ __device__ __forceinline__ int eb_cols(int nx) { return (nx + kEbX - 1) / kEbX; }

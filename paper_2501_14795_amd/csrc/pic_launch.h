@@ -23,4 +23,17 @@ inline int settle_threads(int64_t n, int64_t n_tiles, int most)
     return t;
 }
 
+// A grid of at least `blocks` workgroups of `threads` with less than 2^32
+// threads on an axis: the blocks in a row, or in equal rows where one row would
+// be too long.  A kernel takes its linear index and ends past the last block.
+struct BlockGrid {
+    unsigned x, y;
+};
+inline BlockGrid block_grid(int64_t blocks, int threads)
+{
+    const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+    const int64_t rows = blocks <= most ? 1 : (blocks + most - 1) / most;
+    return BlockGrid{(unsigned)((blocks + rows - 1) / rows), (unsigned)rows};
+}
+
 }  // namespace pic

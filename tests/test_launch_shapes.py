@@ -15,6 +15,12 @@ LIMIT = 1 << 32
 SOURCE = """
 #include "pic_launch.h"
 extern "C" int settle_threads(int64_t n, int64_t n_tiles, int most) { return pic::settle_threads(n, n_tiles, most); }
+extern "C" void block_grid(int64_t blocks, int threads, unsigned *out)
+{
+    const pic::BlockGrid g = pic::block_grid(blocks, threads);
+    out[0] = g.x;
+    out[1] = g.y;
+}
 """
 
 
@@ -27,6 +33,7 @@ def shapes(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, str(d / "s.cpp"), "-o",
                     str(d / "s.so")], check=True)
     lib = ctypes.CDLL(str(d / "s.so"))
+    lib.block_grid.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_uint)]
     lib.settle_threads.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     return lib
 
@@ -48,3 +55,16 @@ def test_settle_threads(shapes):
             # a batch: four tiles per block, at most as many sections as its push has workgroups
             nt = shapes.settle_threads(n, tiles, 256)
             assert nt <= 256 and -(-tiles // 4) * 4 * nt < LIMIT, (tiles, n)
+
+
+def test_block_grid(shapes):
+    out = (ctypes.c_uint * 2)()
+    for threads in (256, 640, 1024):
+        most = (LIMIT - 1) // threads
+        # four species' plan blocks on the largest grid beside its field blocks, and about the border
+        for blocks in [1, 5, 4096, most - 1, most, most + 1, 2 * most + 1, 4095 * 4095 + 32760 * 32760 // 512]:
+            shapes.block_grid(blocks, threads, out)
+            x, y = out
+            assert x * threads < LIMIT and 1 <= y <= 65535
+            assert (x - 1) * y < blocks <= x * y < 1 << 31
+            assert y == 1 or blocks > most
