@@ -372,9 +372,9 @@ int pic_diag(pic_sim *sim, unsigned what, pic_diag_out *out, hipStream_t stream)
  * diagnostic (binomially filtered when pic_config.j_filter > 0).  Each
  * Poisson problem is solved in FP64 until ||r|| <= tol ||r0|| (tol <= 0:
  * 1e-12); the result is stored in FP32.  max_iter <= 0: directly, by Hartley
- * transforms, and again on the residual while that is above tol (each such
- * solve counts as one iteration; at most 20 max(nx, ny) + 100).  max_iter > 0:
- * by at most max_iter iterations of conjugate gradients.
+ * transforms, and again on the residual while that is above tol and the last
+ * solve at least halved it (each such solve counts as one iteration).
+ * max_iter > 0: by at most max_iter iterations of conjugate gradients.
  * scratch: device memory of at least PIC_GAUSS_SCRATCH_BYTES(nx, ny) bytes,
  * 256-byte aligned, caller-owned.  Synchronises `stream`.  out (may be NULL)
  * receives the iterations and final relative residual of both solves.

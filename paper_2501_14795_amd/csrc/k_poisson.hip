@@ -13,7 +13,7 @@
 // solve is direct: two transforms there (rows, columns), the division, two
 // back, each a dense matrix product in FP64 on the matrix cores, repeated on
 // the residual until that is below the tolerance (each pass gains about
-// eleven digits, so once or twice).
+// eleven digits, so once or twice) or no longer falls.
 //
 // Conjugate gradients remain for a caller that caps the iterations.  Every
 // scalar stays on the device: each dot product is a per-block partial sum
@@ -356,7 +356,7 @@ CgResult cg_project(float *fld, const double *rho, double rho_bar, int magnetic,
         const dim3 tiles((nx + kHt - 1) / kHt, (ny + kHt - 1) / kHt);
         hipLaunchKernelGGL(k_hartley_tables, dim3((nx + ny + kCgBlock - 1) / kCgBlock), dim3(kCgBlock), 0, s, w.tab, nx,
                            ny, idx, idy);
-        while (k < max_iter) {
+        for (double last = rr0;; last = rr) {
             hipLaunchKernelGGL((k_hartley<false, false>), tiles, dim3(kHThreads), 0, s, w.r, w.p, w.tab, nx, ny);
             hipLaunchKernelGGL((k_hartley<true, true>), tiles, dim3(kHThreads), 0, s, w.p, w.q, w.tab, nx, ny);
             hipLaunchKernelGGL((k_hartley<false, false>), tiles, dim3(kHThreads), 0, s, w.q, w.p, w.tab, nx, ny);
@@ -370,7 +370,9 @@ CgResult cg_project(float *fld, const double *rho, double rho_bar, int magnetic,
                 res.iterations = -1;
                 return res;
             }
-            if (!(rr > goal)) break;   // reached, or not a number
+            // reached, not a number, or at the rounding left in the constant mode,
+            // which no pass takes out (a pass gains many digits until then)
+            if (!(rr > goal) || rr > 0.25 * last) break;
         }
     }
     while (!direct && k < max_iter) {

@@ -381,7 +381,6 @@ int solve_gauss_in(pic_sim *S, double *d, double tol, int max_iter, pic_gauss_ou
     // a caller's cap counts iterations of conjugate gradients; without one the
     // direct solve, far faster at every size
     const bool direct = max_iter <= 0;
-    if (direct) max_iter = 20 * (c.nx > c.ny ? c.nx : c.ny) + 100;
     CgScratch w;
     w.x = d;
     w.r = d + P;
