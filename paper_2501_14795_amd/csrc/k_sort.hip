@@ -957,11 +957,12 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_add_base_b(const SortArgs *
     const int4 w = it[blockIdx.x];
     sort_add_unit(d[w.x], w.y, w.z);
 }
-// the kSortWaves tiles of an item side by side, 1 << sh threads each
+// the kSortWaves tiles of an item, 1 << sh threads each, by a block or (a row
+// of the grid per part) several
 __global__ void __launch_bounds__(kSettleBlock) k_settle_b(const SortArgs *d, const int4 *it, int sh, int rebase)
 {
     const int4 w = it[blockIdx.x];
-    const int q = threadIdx.x >> sh;
+    const int q = blockIdx.y * (blockDim.x >> sh) + (threadIdx.x >> sh);
     settle_tile(d[w.x], w.y, w.z * kSortWaves + q, threadIdx.x & ((1 << sh) - 1), 1 << sh, rebase != 0);
 }
 
@@ -1071,8 +1072,9 @@ void launch_settle(const SortArgs &a, int n_tiles, bool rebase, hipStream_t s)
 void launch_settle_batch(const SortBatch &b, int64_t particles, int64_t sections, bool rebase, hipStream_t s)
 {
     if (b.n_plan == 0) return;
-    const int nt = settle_threads(particles, sections, kSettleBlock / kSortWaves);
-    hipLaunchKernelGGL(k_settle_b, dim3(b.n_plan), dim3(nt * kSortWaves), 0, s, b.descs, b.plan_items,
+    const int nt = settle_threads(particles, sections, kSettleBlock);
+    const int block = std::min(std::max(nt, kBlock), nt * kSortWaves);
+    hipLaunchKernelGGL(k_settle_b, dim3(b.n_plan, nt * kSortWaves / block), dim3(block), 0, s, b.descs, b.plan_items,
                        __builtin_ctz(nt), rebase ? 1 : 0);
 }
 

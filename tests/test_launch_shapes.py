@@ -48,13 +48,12 @@ def test_settle_threads(shapes):
         for n in PARTICLES:
             nt = shapes.settle_threads(n, tiles, 1024)
             assert nt in (16, 32, 64, 128, 256, 512, 1024)
-            assert nt == 1024 or 8 * nt * tiles >= n      # two passes of four per thread
-            assert nt == 16 or 4 * nt * tiles < n         # and half as many would not do
+            assert nt == 1024 or 16 * nt * tiles >= n     # four passes of four per thread
+            assert nt == 16 or 8 * nt * tiles < n         # and half as many would not do
             block = max(nt, 256)
             assert -(-tiles // (block // nt)) * block < LIMIT, (tiles, n)
-            # a batch: four tiles per block, at most as many sections as its push has workgroups
-            nt = shapes.settle_threads(n, tiles, 256)
-            assert nt <= 256 and -(-tiles // 4) * 4 * nt < LIMIT, (tiles, n)
+            # a batch: items of four tiles, each by one block or (on the second axis) several
+            assert -(-tiles // 4) * min(block, 4 * nt) < LIMIT, (tiles, n)
 
 
 def test_block_grid(shapes):
