@@ -313,13 +313,13 @@ __device__ __forceinline__ bool tcell_inside(int lc, int T)
 constexpr int kPlanBatch = 2;
 static_assert(kMaxWaves + 14 <= 32, "sort plan lists");
 
-__device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int grp)
+__device__ __forceinline__ void sort_plan_unit(const SortArgs &a, int spi, int t0)
 {
     constexpr int NB = kPlanBatch;
     const int lane = threadIdx.x & 63;
     // one tile per wavefront: the index is wavefront-uniform (scalar registers)
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = grp * kSortWaves + wv;
+    const int t = t0 + wv;
     const SortSpecies &sp = a.sp[spi];
     const int n_tiles = a.n_tiles;
 
@@ -866,41 +866,35 @@ __global__ void __launch_bounds__(kSettleBlock) k_settle(SortArgs a, int sh, int
     const int q = threadIdx.x >> sh;
     settle_tile(a, blockIdx.y, blockIdx.x * (blockDim.x >> sh) + q, threadIdx.x & ((1 << sh) - 1), 1 << sh, rebase != 0);
 }
-__global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a) { sort_plan_unit(a, blockIdx.y, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a)
+{
+    sort_plan_unit(a, blockIdx.y, blockIdx.x * kSortWaves);
+}
 
-// The plan and the field half (of a large grid its E step) in one launch: they touch disjoint data, and
-// the plan's wavefronts, which mostly wait, share the chip with the field
-// half's stream.  n_plan plan blocks, one after every `every` - 1 others.
+// The plan and the field half (of a large grid its E step) in one launch: they
+// touch disjoint data, and the plan's wavefronts, which mostly wait, share the
+// chip with the field half's stream.  The plan's blocks come first, a tile per
+// wavefront of the whole block; the field's fill the chip as they drain.
 // (As two chains on two streams the same work paid for the second chain's
 // launches and two event waits: a 64 x 64 step 53 us, now 38; a 512^2 two-beam
-// step 383, now 366.)
+// step 383, now 366.)  us a step with the plan's blocks of four tiles spread
+// between the field's / four tiles, first / ten tiles, spread / ten, first:
+// 2048^2 32 x 32 tiles 796 / 789 / 798 / 788; 1408^2 16 x 16 tiles 427 / 423 /
+// 436 / 420; 1024^2 16 x 16, 64 particles a cell 696 / 692 / 695 / 686.
 struct PlanMix {
-    int n, n_plan, every;   // blocks, plan blocks
-    // the block's plan index, or -1 and its field index in `field`
-    __device__ __forceinline__ int plan_of(int b, int &field) const
-    {
-        const int p = b / every;
-        if (b - p * every == 0 && p < n_plan) return p;
-        field = b - min(n_plan, p + 1);
-        return -1;
-    }
+    int n, n_plan;   // blocks, plan blocks
+    int tiles;       // tiles per plan block
 };
-static PlanMix plan_mix(int n_plan, int n_field)
-{
-    return PlanMix{n_plan + n_field, n_plan, std::max(1, (n_plan + n_field) / n_plan)};
-}
 
 template <bool FUSED, bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs f, PlanMix mix)
 {
-    int q;
-    const int b = linear_block();
-    if (b >= mix.n) return;
-    const int p = mix.plan_of(b, q);
-    if (p >= 0) {
-        if (threadIdx.x >= kBlock) return;   // the plan's block is smaller (an ended wavefront holds up no barrier)
+    const int p = linear_block(), q = p - mix.n_plan;
+    if (p >= mix.n) return;
+    if (q < 0) {
+        if ((int)threadIdx.x >= 64 * mix.tiles) return;   // (an ended wavefront holds up no barrier)
         const int groups = mix.n_plan / a.n_species;
-        sort_plan_unit(a, p / groups, p % groups);
+        sort_plan_unit(a, p / groups, p % groups * mix.tiles);
     } else if constexpr (FUSED) {
         const int cols = eb_cols(f.nx);
         field_eb_region<FOLD, T, H>(f, q % cols, q / cols);
@@ -913,14 +907,12 @@ template <bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd, const int4 *si, const FieldArgs *fd,
                                                          const int4 *fi, PlanMix mix)
 {
-    int q;
-    const int b = linear_block();
-    if (b >= mix.n) return;
-    const int p = mix.plan_of(b, q);
-    if (p >= 0) {
-        if (threadIdx.x >= kBlock) return;
+    const int p = linear_block(), q = p - mix.n_plan;
+    if (p >= mix.n) return;
+    if (q < 0) {
+        if ((int)threadIdx.x >= 64 * mix.tiles) return;
         const int4 w = si[p];
-        sort_plan_unit(sd[w.x], w.y, w.z);
+        sort_plan_unit(sd[w.x], w.y, w.z * kSortWaves);
     } else {
         const int4 w = fi[q];
         field_eb_region<FOLD, T, H>(fd[w.x], w.y, w.z);
@@ -951,6 +943,13 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_add_direct_b(const SortArgs
 {
     const int4 w = it[blockIdx.x];
     sort_add_direct_unit(d[w.x], w.y, w.z);
+}
+__global__ void __launch_bounds__(kBlock) k_sort_plan_b(const SortArgs *d, const int4 *it, int n)
+{
+    const int b = linear_block();
+    if (b >= n) return;
+    const int4 w = it[b];
+    sort_plan_unit(d[w.x], w.y, w.z * kSortWaves);
 }
 __global__ void __launch_bounds__(kScanBlock) k_sort_add_base_b(const SortArgs *d, const int4 *it)
 {
@@ -1105,7 +1104,7 @@ namespace {
 struct PlanFieldLaunch {
     const SortArgs *a;       // single
     const FieldArgs *f;
-    int n_plan, n_field;
+    int n_plan, n_field, tiles;
     const SortBatch *b;      // batched
     const FieldArgs *fd;
     const int4 *fi;
@@ -1113,7 +1112,7 @@ struct PlanFieldLaunch {
     template <bool FOLD, int T, int H>
     void run() const
     {
-        const PlanMix mix = plan_mix(n_plan, n_field);
+        const PlanMix mix{n_plan + n_field, n_plan, tiles};
         const BlockGrid g = block_grid(mix.n, kEbThreads);
         const dim3 grid(g.x, g.y);
         if (a && f->eedge) {
@@ -1129,13 +1128,30 @@ struct PlanFieldLaunch {
 
 }  // namespace
 
+constexpr int kChipWaves = 256 * 32;   // wavefronts the device holds
+
 void launch_plan_and_field(const SortArgs &args, int n_tiles, const FieldArgs &f, int tile, int halo, hipStream_t s)
 {
+    // Two launches where the plan alone fills the chip twice over (8,192
+    // wavefronts): the field half's blocks then find no free places and only
+    // slow the plan's reads.  us a step, one launch / two: 65,536 tiles (2048^2, 8 x 8,
+    // one particle a cell) 770 / 746; 16,384 (2048^2 16 x 16, 16 particles)
+    // 872 / 870, (1024^2 8 x 8, one and 16) 182 / 180, 360 / 358; 7,744 420 / 423.
+    if ((int64_t)n_tiles * args.n_species >= 2 * kChipWaves) {
+        launch_sort_plan(args, n_tiles, s);
+        launch_field_half(f, tile, halo, s);
+        return;
+    }
     SortArgs a = args;
     a.scan = scan_mode((n_tiles + kScanBlock - 1) / kScanBlock);
-    const int n_plan = (n_tiles + kSortWaves - 1) / kSortWaves * a.n_species;
+    // a wavefront for every tile of a full block; of fewer tiles per block as
+    // long as there is no block for every compute unit (1,024 tiles of 8 x 8: 28.3 us
+    // a step with four a block, 29.2 with ten), and of as many as the threads of
+    // its scan where a block counts all tiles itself
+    const int tiles = (int64_t)n_tiles * a.n_species < 256 * (kEbThreads / 64) ? kSortWaves : kEbThreads / 64;
+    const int n_plan = (n_tiles + tiles - 1) / tiles * a.n_species;
     const int n_field = f.eedge ? eb_cols(f.nx) * eb_rows(f.ny) : e_blocks(f.nx, f.ny);
-    eb_dispatch(PlanFieldLaunch{&a, &f, n_plan, n_field, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,
+    eb_dispatch(PlanFieldLaunch{&a, &f, n_plan, n_field, tiles, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,
                 tile, halo);
 }
 
@@ -1143,7 +1159,18 @@ void launch_plan_and_field_batch(const SortBatch &b, const FieldArgs *fields, co
                                  bool fold, int tile, int halo, hipStream_t s)
 {
     if (b.n_plan == 0) return;
-    eb_dispatch(PlanFieldLaunch{nullptr, nullptr, b.n_plan, n_regions, &b, fields, regions, s}, fold, tile,
+    // Two launches where the plan fills the chip (its blocks have four tiles in
+    // the places of ten, so the line lies lower than above).  us for two steps, one
+    // launch / two: 64 members with about 5,000 tiles 1006 / 1020, 128 with 10,000
+    // 2341 / 2336; 2 x 1024^2 16 x 16 tiles (8,192) 454 / 446; 48 and 128
+    // of 8 x 8 tiles (15,000 and 40,000) 437 / 427, 1361 / 1281.
+    if ((int64_t)b.n_plan * kSortWaves >= kChipWaves) {
+        const BlockGrid g = block_grid(b.n_plan, kBlock);
+        hipLaunchKernelGGL(k_sort_plan_b, dim3(g.x, g.y), dim3(kBlock), 0, s, b.descs, b.plan_items, b.n_plan);
+        launch_field_half_batch(fields, regions, n_regions, fold, tile, halo, s);
+        return;
+    }
+    eb_dispatch(PlanFieldLaunch{nullptr, nullptr, b.n_plan, n_regions, kSortWaves, &b, fields, regions, s}, fold, tile,
                 halo);
 }
 
