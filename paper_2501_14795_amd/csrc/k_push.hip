@@ -752,10 +752,13 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     __shared__ V1 s_bz[NE * NE];
     __shared__ uint32_t s_lb[P ? W : 1][7][P ? kLeaverBuf : 1];   // packed layout: leaver entry + new data
     __shared__ Acc s_j[R][3 * JP];
-    __shared__ int s_dir[kMaxSpecies][W][9];   // leavers per wavefront and direction
+    __shared__ int s_dir[kMaxSpecies][9];   // leavers per direction
     __shared__ int s_wl[kMaxSpecies][W];
     __shared__ uint32_t s_pq[W][6][kMotionBuf];   // queued face-crossing motions
     __shared__ int s_fill[W][64];                  // pending holes of the chunk being loaded
+    // the first leaver entries each wavefront finds (of all species, in turn):
+    // the lists by direction are made of them without waiting for memory
+    __shared__ uint32_t s_le[W][kEntryBuf];
     // per species: the tile's section [begin, end) and its pending fill, and
     // each wavefront's first hole of it; read with the halo, so that neither
     // the particle loop's start nor the records after it wait for memory again
@@ -770,13 +773,13 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t plane = (int64_t)a.nx * a.ny;
 
-    // (kMaxSpecies W <= NT; the descriptor index is clamped to the species there are)
-    const int qs = min(tid / W, a.n_species - 1), qw = tid % W;
+    // wavefront s: species s
+    static_assert(kMaxSpecies <= W, "a wavefront per species");
     int sec = 0, sfb = 0;
-    if (tid < a.n_species * W) {
-        const PIC_GLOBAL int32_t *v = qw < 2 ? gp(a.sp[qs].off) + tile + qw : gp(a.sp[qs].fcount) + tile;
-        if (qw < 3) sec = *v;
-        sfb = gp(a.sp[qs].fbase)[(int64_t)tile * W + qw];
+    if (wave < a.n_species) {
+        const SpeciesDev &sp = a.sp[wave];
+        if (lane < 3) sec = *(lane < 2 ? gp(sp.off) + tile + lane : gp(sp.fcount) + tile);
+        if (lane < W) sfb = gp(sp.fbase)[(int64_t)tile * W + lane];
     }
     for (int e = tid; e < NE * NE; e += NT) {
         const int r = e / NE, c = e - r * NE;
@@ -797,10 +800,10 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
         }
     }
     for (int e = tid; e < R * 3 * JP; e += NT) (&s_j[0][0])[e] = Acc(0);
-    for (int e = tid; e < kMaxSpecies * W * 9; e += NT) (&s_dir[0][0][0])[e] = 0;
-    if (tid < a.n_species * W) {
-        if (qw < 3) s_sec[qs][qw] = sec;
-        s_fb[qs][qw] = sfb;
+    if (tid < kMaxSpecies * 9) (&s_dir[0][0])[tid] = 0;
+    if (wave < a.n_species) {
+        if (lane < 3) s_sec[wave][lane] = sec;
+        if (lane < W) s_fb[wave][lane] = sfb;
     }
     __syncthreads();
 
@@ -813,6 +816,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     bool from_stg = false;
     if constexpr (MS) from_stg = *gp(a.stg_live) != 0;
 
+    int ebase = 0;   // leavers of the species before (wavefront-uniform)
     for (int s = 0; s < a.n_species; ++s) {
         const SpeciesDev sp = a.sp[s];
         const int begin = __builtin_amdgcn_readfirstlane(s_sec[s][0]), end = __builtin_amdgcn_readfirstlane(s_sec[s][1]);
@@ -930,23 +934,28 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                         }
                         if (leaver) {
                             const int r = nbuf + lane_rank(mk);
-                            s_lb[wave][0][r] = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
+                            const uint32_t v = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
+                            if (ebase + nleav + r < kEntryBuf) s_le[wave][ebase + nleav + r] = v;
+                            s_lb[wave][0][r] = v;
                             s_lb[wave][1][r] = (uint32_t)m.ncell;
                             s_lb[wave][2][r] = __float_as_uint(m.xn);
                             s_lb[wave][3][r] = __float_as_uint(m.yn);
                             s_lb[wave][4][r] = __float_as_uint(m.ux);
                             s_lb[wave][5][r] = __float_as_uint(m.uy);
                             s_lb[wave][6][r] = __float_as_uint(m.uz);
-                            atomicAdd(&s_dir[s][wave][m.dir], 1);
+                            atomicAdd(&s_dir[s][m.dir], 1);
                         }
                         nbuf += c;
                     }
                 } else {
                     if (leaver) {
-                        const int64_t q = (int64_t)lo + nleav + lane_rank(mk);
-                        gp(sp.leav)[q] = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
+                        const int r = nleav + lane_rank(mk);
+                        const int64_t q = (int64_t)lo + r;
+                        const uint32_t v = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
+                        if (ebase + r < kEntryBuf) s_le[wave][ebase + r] = v;
+                        gp(sp.leav)[q] = v;
                         put_leaver(sp.lrec, q, m.ncell, m.xn, m.yn, m.ux, m.uy, m.uz);
-                        atomicAdd(&s_dir[s][wave][m.dir], 1);
+                        atomicAdd(&s_dir[s][m.dir], 1);
                     }
                     nleav += __popcll(mk);
                 }
@@ -994,6 +1003,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
             }
         }
         if (lane == 0) s_wl[s][wave] = nleav;
+        ebase += nleav;
     }
     __syncthreads();
     // the fill the last sort left is done
@@ -1004,16 +1014,59 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
         if (tile == a.ntx * a.nty - 1) gp(a.sp[tid].offp)[tile + 1] = s_sec[tid][1];
     }
 
-    // the first 64 entries of the wavefront's leaver sub-lists of two species,
-    // on their way while the current is written out
-    uint32_t lpre[2] = {0u, 0u};
+    // The tile's leavers by direction, for the sort: the s-th wavefront from the
+    // last (the first has the records) lists those of species s, 64 of all the
+    // sub-lists in a row per pass (lane d: the next position of direction d),
+    // before it joins in writing the current out.  About 200 instructions a tile
+    // spare the sort plan three of four candidates it would read otherwise.  us a
+    // push without the lists / every wavefront placing its own sub-list, behind
+    // the current's stores, from entries read back / this: 65,536 8 x 8 tiles
+    // of 64 particles 517 / 560 / 499; 16,384 16 x 16 of 4,096 718 / 738 / 710;
+    // 4,096 32 x 32 of 16,384 675 / 681 / 677.
+    if (const int s = W - 1 - wave; s < a.n_species && a.sp[s].dlist) {
+        const SpeciesDev &sp = a.sp[s];
+        const int begin = __builtin_amdgcn_readfirstlane(s_sec[s][0]), end = __builtin_amdgcn_readfirstlane(s_sec[s][1]);
+        int pos = 0, total = 0;
+        const int c = lane < 9 ? s_dir[s][lane] : 0;
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-        if (s < a.n_species && a.sp[s].dlist && lane < s_wl[s][wave]) {
-            int lo, hi;
-            wave_range(s_sec[s][0], s_sec[s][1], wave, W, lo, hi);
-            lpre[s] = gp(a.sp[s].leav)[lo + lane];
+        for (int d = 0; d < 9; ++d) {
+            const int v = __builtin_amdgcn_readlane(c, d);
+            if (d < lane) pos += v;
+            total += v;
         }
+        for (int c0 = 0; c0 < total; c0 += 64) {
+            // entry k is the (k - first)-th of wavefront w's sub-list
+            const int k = c0 + lane;
+            const bool in = k < total;
+            int w = 0, first = 0, next = 0;
+            for (int u = 0; u < W - 1; ++u) {
+                next += s_wl[s][u];
+                if (k >= next) {
+                    w = u + 1;
+                    first = next;
+                }
+            }
+            int e0 = k - first;
+            int lo, hi;
+            wave_range(begin, end, w, W, lo, hi);
+            const int e = lo + e0;
+            for (int q = 0; q < s; ++q) e0 += s_wl[q][w];   // (the species before it, in its buffer)
+            uint32_t v = 0u;
+            if (in) v = e0 < kEntryBuf ? s_le[w][e0] : gp(sp.leav)[e];
+            const int d = in ? (int)(v & 15u) : 9;
+            int at = 0, taken = 0;
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                const unsigned long long m = __ballot(d == j);
+                if (d == j) at = lane_rank(m);
+                if (lane == j) taken = __popcll(m);
+            }
+            at += __shfl(pos, d, 64);
+            if (in)
+                ((PIC_GLOBAL vi2a *)sp.dlist)[((int64_t)begin + at) * kListStride] = vi2a{(int)(v >> 4), e - begin};
+            pos += taken;
+        }
+    }
 
     // the int64 current sums are exact while the tile holds fewer than 2^31
     // particles over all species
@@ -1029,10 +1082,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
         int leavers = 0;
         for (int w = 0; w < W; ++w) leavers += s_wl[s][w];
         int v = 0;
-        int dir = 0;
-        if (k < 9)
-            for (int w = 0; w < W; ++w) dir += s_dir[s][w][k];
-        if (k < 9) v = (k == 4) ? n - leavers : dir;
+        if (k < 9) v = (k == 4) ? n - leavers : s_dir[s][k];
         else if (k == kCntLeavers) v = leavers;
         else if (k < kCntSub + W) v = s_wl[s][k - kCntSub];
         gp(a.sp[s].cnt)[(int64_t)tile * kCntStride + k] = v;
@@ -1096,49 +1146,6 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
             bh[g] = b.x;
             bh[plane + g] = b.y;
             bh[2 * plane + g] = b.z;
-        }
-    }
-    // The tile's leavers by direction, for the sort: each wavefront places its
-    // sub-list's entries behind those of the wavefronts before it (lane d: the
-    // next position of direction d).  About 60 instructions per 64 leavers here
-    // spare the sort plan three of four candidates it would read otherwise.
-    for (int s = 0; s < a.n_species; ++s) {
-        const int mine = s_wl[s][wave];   // wavefront-uniform
-        const SpeciesDev &sp = a.sp[s];
-        if (mine == 0 || !sp.dlist) continue;
-        const int begin = s_sec[s][0];
-        int lo, hi;
-        wave_range(begin, s_sec[s][1], wave, W, lo, hi);
-        int pos = 0, all = 0;
-        if (lane < 9)
-            for (int w = 0; w < W; ++w) {
-                const int v = s_dir[s][w][lane];
-                pos += w < wave ? v : 0;
-                all += v;
-            }
-#pragma unroll
-        for (int d = 0; d < 9; ++d) {
-            const int v = __builtin_amdgcn_readlane(all, d);
-            if (d < lane) pos += v;
-        }
-        for (int c0 = 0; c0 < mine; c0 += 64) {
-            const bool in = c0 + lane < mine;
-            const int e = lo + c0 + lane;
-            uint32_t v = 0u;
-            if (s < 2 && c0 == 0) v = s == 0 ? lpre[0] : lpre[1];
-            else if (in) v = gp(sp.leav)[e];
-            const int d = in ? (int)(v & 15u) : 9;
-            int at = 0, taken = 0;
-#pragma unroll
-            for (int k = 0; k < 9; ++k) {
-                const unsigned long long m = __ballot(d == k);
-                if (d == k) at = lane_rank(m);
-                if (lane == k) taken = __popcll(m);
-            }
-            at += __shfl(pos, d, 64);
-            if (in)
-                ((PIC_GLOBAL vi2a *)sp.dlist)[((int64_t)begin + at) * kListStride] = vi2a{(int)(v >> 4), e - begin};
-            pos += taken;
         }
     }
 }

@@ -103,6 +103,7 @@ __host__ __device__ constexpr int shape_pad(int DM) { return DM == kDepQuad ? 1 
 constexpr int kLdsBytes = 160 * 1024;   // LDS of one gfx950 compute unit
 constexpr int kMotionBuf = 64;           // queued face-crossing motions per wavefront
 constexpr int kLeaverBuf = 64;           // leavers buffered per wavefront (packed layout)
+constexpr int kEntryBuf = 64;            // leaver entries kept in LDS per wavefront
 // one ballot can add a whole wavefront to either buffer
 static_assert(kMotionBuf >= 64 && kLeaverBuf >= 64, "per-wavefront LDS buffers must hold 64 entries");
 
@@ -115,8 +116,8 @@ constexpr int push_lds_bytes(int T, int R, int JM, int H = 1, int W = 0)
     if (W == 0) W = push_waves(T);
     return (T + 2 * H) * (T + 2 * H) * (push_packed(T) ? 48 : 24) +
            R * 3 * (T + 2 * H + 1) * (T + 2 * H + 1) * (JM == kJFixed ? 8 : 4) +
-           kMaxSpecies * (9 * W + W + W + 3) * 4 + W * 6 * kMotionBuf * 4 +
-           (push_packed(T) ? W * 7 * kLeaverBuf * 4 : 0) + W * 64 * 4;
+           kMaxSpecies * (9 + W + W + 3) * 4 + W * 6 * kMotionBuf * 4 +
+           (push_packed(T) ? W * 7 * kLeaverBuf * 4 : 0) + W * 64 * 4 + W * kEntryBuf * 4;
 }
 
 // Sort cadences the push kernel is built for: every 1, 2 or 4 steps, with
