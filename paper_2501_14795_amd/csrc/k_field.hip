@@ -63,7 +63,7 @@ __global__ void __launch_bounds__(kEbThreads) k_field_half(FieldArgs a)
 
 // The E step alone, for a large grid.
 template <bool FOLD, int T, int H>
-__global__ void __launch_bounds__(kEbThreads) k_field_e(FieldArgs a)
+__global__ void __launch_bounds__(kEThreads) k_field_e(FieldArgs a)
 {
     field_e_block<FOLD, T, H>(a, blockIdx.x);
 }
@@ -95,7 +95,7 @@ struct FieldLaunch {
     void run() const
     {
         if (single && !single->eedge) {
-            hipLaunchKernelGGL((k_field_e<FOLD, T, H>), dim3(e_blocks(single->nx, single->ny)), dim3(kEbThreads), 0, s,
+            hipLaunchKernelGGL((k_field_e<FOLD, T, H>), dim3(e_blocks(single->nx, single->ny)), dim3(kEThreads), 0, s,
                                *single);
             launch_field_b(*single, s);
         } else if (single)

@@ -876,8 +876,8 @@ __global__ void __launch_bounds__(kBlock) k_sort_plan(SortArgs a)
 // chip with the field half's stream.  The plan's blocks come first, a tile per
 // wavefront of the whole block; the field's fill the chip as they drain.
 // (As two chains on two streams the same work paid for the second chain's
-// launches and two event waits: a 64 x 64 step 53 us, now 38; a 512^2 two-beam
-// step 383, now 366.)  us a step with the plan's blocks of four tiles spread
+// launches and two event waits: a 64 x 64 step 53 us, now 29; a 512^2 two-beam
+// step 383, now 358.)  us a step with the plan's blocks of four tiles spread
 // between the field's / four tiles, first / ten tiles, spread / ten, first:
 // 2048^2 32 x 32 tiles 796 / 789 / 798 / 788; 1408^2 16 x 16 tiles 427 / 423 /
 // 436 / 420; 1024^2 16 x 16, 64 particles a cell 696 / 692 / 695 / 686.
@@ -886,7 +886,7 @@ struct PlanMix {
     int tiles;       // tiles per plan block
 };
 
-template <bool FUSED, bool FOLD, int T, int H>
+template <bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs f, PlanMix mix)
 {
     const int p = linear_block(), q = p - mix.n_plan;
@@ -895,13 +895,30 @@ __global__ void __launch_bounds__(kEbThreads) k_plan_field(SortArgs a, FieldArgs
         if ((int)threadIdx.x >= 64 * mix.tiles) return;   // (an ended wavefront holds up no barrier)
         const int groups = mix.n_plan / a.n_species;
         sort_plan_unit(a, p / groups, p % groups * mix.tiles);
-    } else if constexpr (FUSED) {
+    } else {
         const int cols = eb_cols(f.nx);
         field_eb_region<FOLD, T, H>(f, q % cols, q / cols);
+    }
+}
+
+// The same with the E step alone of a large grid: no block is larger than the
+// plan's four wavefronts, so the two kinds take each other's places freely.
+// us a step, blocks of ten wavefronts or, from 16,384 tiles on, two launches /
+// this: 2048^2 32 x 32 tiles 767 / 763, with one particle a cell 213 / 203;
+// 16 x 16 840 / 830 and 303 / 290; 8 x 8, one a cell 687 / 672.
+template <bool FOLD, int T, int H>
+__global__ void __launch_bounds__(kBlock) k_plan_e(SortArgs a, FieldArgs f, PlanMix mix)
+{
+    const int p = linear_block(), q = p - mix.n_plan;
+    if (p >= mix.n) return;
+    if (q < 0) {
+        const int groups = mix.n_plan / a.n_species;
+        sort_plan_unit(a, p / groups, p % groups * kSortWaves);
     } else {
         field_e_block<FOLD, T, H>(f, q);
     }
 }
+static_assert(kEThreads == kBlock, "a block of either kind");
 
 template <bool FOLD, int T, int H>
 __global__ void __launch_bounds__(kEbThreads) k_plan_field_b(const SortArgs *sd, const int4 *si, const FieldArgs *fd,
@@ -1113,13 +1130,14 @@ struct PlanFieldLaunch {
     void run() const
     {
         const PlanMix mix{n_plan + n_field, n_plan, tiles};
-        const BlockGrid g = block_grid(mix.n, kEbThreads);
+        const bool large = a && !f->eedge;
+        const BlockGrid g = block_grid(mix.n, large ? kBlock : kEbThreads);
         const dim3 grid(g.x, g.y);
-        if (a && f->eedge) {
-            hipLaunchKernelGGL((k_plan_field<true, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
-        } else if (a) {   // a large grid: E here, the second B half step after it
-            hipLaunchKernelGGL((k_plan_field<false, FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
+        if (large) {   // the second B half step after E
+            hipLaunchKernelGGL((k_plan_e<FOLD, T, H>), grid, dim3(kBlock), 0, s, *a, *f, mix);
             launch_field_b(*f, s);
+        } else if (a) {
+            hipLaunchKernelGGL((k_plan_field<FOLD, T, H>), grid, dim3(kEbThreads), 0, s, *a, *f, mix);
         } else
             hipLaunchKernelGGL((k_plan_field_b<FOLD, T, H>), grid, dim3(kEbThreads), 0, s, b->descs, b->plan_items, fd,
                                fi, mix);
@@ -1132,12 +1150,12 @@ constexpr int kChipWaves = 256 * 32;   // wavefronts the device holds
 
 void launch_plan_and_field(const SortArgs &args, int n_tiles, const FieldArgs &f, int tile, int halo, hipStream_t s)
 {
+    const int64_t sections = (int64_t)n_tiles * args.n_species;
     // Two launches where the plan alone fills the chip twice over (8,192
-    // wavefronts): the field half's blocks then find no free places and only
-    // slow the plan's reads.  us a step, one launch / two: 65,536 tiles (2048^2, 8 x 8,
-    // one particle a cell) 770 / 746; 16,384 (2048^2 16 x 16, 16 particles)
-    // 872 / 870, (1024^2 8 x 8, one and 16) 182 / 180, 360 / 358; 7,744 420 / 423.
-    if ((int64_t)n_tiles * args.n_species >= 2 * kChipWaves) {
+    // wavefronts): the field half's blocks of ten then find no free places.  us a
+    // step, one launch / two: 16,384 tiles (1024^2, 8 x 8, one and 16 particles a
+    // cell) 182 / 180, 360 / 358; 7,744 (1408^2, 16 x 16) 420 / 423.
+    if (f.eedge && sections >= 2 * kChipWaves) {
         launch_sort_plan(args, n_tiles, s);
         launch_field_half(f, tile, halo, s);
         return;
@@ -1148,7 +1166,7 @@ void launch_plan_and_field(const SortArgs &args, int n_tiles, const FieldArgs &f
     // long as there is no block for every compute unit (1,024 tiles of 8 x 8: 28.3 us
     // a step with four a block, 29.2 with ten), and of as many as the threads of
     // its scan where a block counts all tiles itself
-    const int tiles = (int64_t)n_tiles * a.n_species < 256 * (kEbThreads / 64) ? kSortWaves : kEbThreads / 64;
+    const int tiles = !f.eedge || sections < 256 * (kEbThreads / 64) ? kSortWaves : kEbThreads / 64;
     const int n_plan = (n_tiles + tiles - 1) / tiles * a.n_species;
     const int n_field = f.eedge ? eb_cols(f.nx) * eb_rows(f.ny) : e_blocks(f.nx, f.ny);
     eb_dispatch(PlanFieldLaunch{&a, &f, n_plan, n_field, tiles, nullptr, nullptr, nullptr, s}, f.jtile != nullptr,

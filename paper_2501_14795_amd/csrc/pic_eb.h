@@ -125,11 +125,12 @@ __device__ __forceinline__ void field_eb_region(const FieldArgs &a, int rx, int 
     f[5 * P + k] = b.z;
 }
 
-// The E step alone of the cells of block q (kEbThreads of them, in index order).
+constexpr int kEThreads = 256;
+// The E step alone of the cells of block q (a thread each, in index order).
 template <bool FOLD, int T, int H>
 __device__ __forceinline__ void field_e_block(const FieldArgs &a, int q)
 {
-    const int64_t P = (int64_t)a.nx * a.ny, k = (int64_t)q * kEbThreads + threadIdx.x;
+    const int64_t P = (int64_t)a.nx * a.ny, k = (int64_t)q * kEThreads + threadIdx.x;
     if (k >= P) return;
     const int j = (int)(k / a.nx), i = (int)(k - (int64_t)j * a.nx);
     PIC_GLOBAL float *f = gp(a.fld);
@@ -144,7 +145,7 @@ __device__ __forceinline__ void field_e_block(const FieldArgs &a, int q)
         for (int c = 0; c < 3; ++c) f[(6 + c) * P + k] = jv[c];
     }
 }
-inline int e_blocks(int nx, int ny) { return (int)(((int64_t)nx * ny + kEbThreads - 1) / kEbThreads); }
+inline int e_blocks(int nx, int ny) { return (int)(((int64_t)nx * ny + kEThreads - 1) / kEThreads); }
 
 // the block's index in a block_grid
 __device__ __forceinline__ int linear_block() { return (int)(blockIdx.x + gridDim.x * blockIdx.y); }

@@ -1,4 +1,4 @@
-"""pic_step, pic_sync and pic_diag on a grid of 6.2 M tiles of 8 x 8 cells and
+"""pic_step, pic_sync and pic_diag on a grid of 13.5 M tiles of 8 x 8 cells and
 four species, whose sort plan and field blocks together are more than 2^32
 threads on one axis.
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 def test_step_on_millions_of_tiles():
     import torch
     from paper_2501_14795_amd import Sim, _lib
-    N, T, DX, DT = 19904, 8, 0.1, 0.07
+    N, T, DX, DT = 29376, 8, 0.1, 0.07
     rng = np.random.default_rng(11)
     species = []
     for k in range(4):

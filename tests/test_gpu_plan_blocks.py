@@ -30,8 +30,8 @@ def _equal(a, b, nspecies, step):
             assert np.array_equal(pa[name], pb[name]), (step, k, name)
 
 
-# tiles: 2,550; 2,601 (a last block of one); 2 x 1,296; 16,383; 16,384; 2 x 8,281
-@pytest.mark.parametrize("ntx,nty,nspecies", [(50, 51, 1), (51, 51, 1), (36, 36, 2), (129, 127, 1), (128, 128, 1),
+# tiles: 2,550; 2,601 (a last block of one); 2 x 1,296; 16,383; 16,384; 32,940 (2.1 M cells: E and B apart); 2 x 8,281
+@pytest.mark.parametrize("ntx,nty,nspecies", [(50, 51, 1), (51, 51, 1), (36, 36, 2), (129, 127, 1), (128, 128, 1), (183, 180, 1),
                                               (91, 91, 2)])
 def test_step_equals_the_separate_calls(ntx, nty, nspecies):
     from paper_2501_14795_amd import Sim
