@@ -935,7 +935,8 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                         if (leaver) {
                             const int r = nbuf + lane_rank(mk);
                             const uint32_t v = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
-                            if (ebase + nleav + r < kEntryBuf) s_le[wave][ebase + nleav + r] = v;
+                            if (ebase + nleav + nbuf < kEntryBuf && ebase + nleav + r < kEntryBuf)
+                                s_le[wave][ebase + nleav + r] = v;
                             s_lb[wave][0][r] = v;
                             s_lb[wave][1][r] = (uint32_t)m.ncell;
                             s_lb[wave][2][r] = __float_as_uint(m.xn);
@@ -952,7 +953,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                         const int r = nleav + lane_rank(mk);
                         const int64_t q = (int64_t)lo + r;
                         const uint32_t v = ((uint32_t)(i - begin) << 4) | (uint32_t)m.dir;
-                        if (ebase + r < kEntryBuf) s_le[wave][ebase + r] = v;
+                        if (ebase + nleav < kEntryBuf && ebase + r < kEntryBuf) s_le[wave][ebase + r] = v;
                         gp(sp.leav)[q] = v;
                         put_leaver(sp.lrec, q, m.ncell, m.xn, m.yn, m.ux, m.uy, m.uz);
                         atomicAdd(&s_dir[s][m.dir], 1);
@@ -1021,8 +1022,10 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
     // spare the sort plan three of four candidates it would read otherwise.  us a
     // push without the lists / every wavefront placing its own sub-list, behind
     // the current's stores, from entries read back / this: 65,536 8 x 8 tiles
-    // of 64 particles 517 / 560 / 499; 16,384 16 x 16 of 4,096 718 / 738 / 710;
-    // 4,096 32 x 32 of 16,384 675 / 681 / 677.
+    // of 64 particles 517 / 560 / 485; 16,384 16 x 16 of 4,096 718 / 738 / 708;
+    // 4,096 32 x 32 of 16,384 681 / 687 / 684; 1,024 16 x 16 of two hot species,
+    // over a thousand leavers each, 380 before, now 385 (all tiles run at once
+    // there, and their last wavefronts' passes end the kernel).
     if (const int s = W - 1 - wave; s < a.n_species && a.sp[s].dlist) {
         const SpeciesDev &sp = a.sp[s];
         const int begin = __builtin_amdgcn_readfirstlane(s_sec[s][0]), end = __builtin_amdgcn_readfirstlane(s_sec[s][1]);
@@ -1034,10 +1037,12 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
             if (d < lane) pos += v;
             total += v;
         }
-        for (int c0 = 0; c0 < total; c0 += 64) {
-            // entry k is the (k - first)-th of wavefront w's sub-list
+        // entry k of the sub-lists in a row (x, and its place y in the tile's
+        // list): the (k - first)-th of wavefront w's
+        auto entry = [&](int c0) {
+            vi2a r{15, 0};
             const int k = c0 + lane;
-            const bool in = k < total;
+            if (k >= total) return r;
             int w = 0, first = 0, next = 0;
             for (int u = 0; u < W - 1; ++u) {
                 next += s_wl[s][u];
@@ -1046,13 +1051,22 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
                     first = next;
                 }
             }
-            int e0 = k - first;
+            int e = k - first;
             int lo, hi;
             wave_range(begin, end, w, W, lo, hi);
-            const int e = lo + e0;
-            for (int q = 0; q < s; ++q) e0 += s_wl[q][w];   // (the species before it, in its buffer)
-            uint32_t v = 0u;
-            if (in) v = e0 < kEntryBuf ? s_le[w][e0] : gp(sp.leav)[e];
+            r.y = lo - begin + e;
+            for (int q = 0; q < s; ++q) e += s_wl[q][w];   // (the species before it, in its buffer)
+            r.x = (int)(e < kEntryBuf ? s_le[w][e] : gp(sp.leav)[begin + r.y]);
+            return r;
+        };
+        // (two passes ahead: what the buffers do not hold comes from memory)
+        vi2a e1 = entry(0), e2 = entry(64);
+        for (int c0 = 0; c0 < total; c0 += 64) {
+            const vi2a e = e1;
+            e1 = e2;
+            e2 = entry(c0 + 128);
+            const bool in = c0 + lane < total;
+            const uint32_t v = (uint32_t)e.x;
             const int d = in ? (int)(v & 15u) : 9;
             int at = 0, taken = 0;
 #pragma unroll
@@ -1063,7 +1077,7 @@ __device__ __forceinline__ void push_tile(const PushArgs &a, const int tile, con
             }
             at += __shfl(pos, d, 64);
             if (in)
-                ((PIC_GLOBAL vi2a *)sp.dlist)[((int64_t)begin + at) * kListStride] = vi2a{(int)(v >> 4), e - begin};
+                ((PIC_GLOBAL vi2a *)sp.dlist)[((int64_t)begin + at) * kListStride] = vi2a{(int)(v >> 4), e.y};
             pos += taken;
         }
     }
