@@ -22,7 +22,7 @@ def _load(ntx, nty, tile, mean, seed):
     return st
 
 
-@pytest.mark.parametrize("mean", [1, 400, 800, 1600, 3500, 6000, 12000])
+@pytest.mark.parametrize("mean", [1, 100, 200, 400, 800, 1600, 6000])
 def test_sync_writes_the_cells(mean):
     import torch
     from paper_2501_14795_amd import Sim, Batch
