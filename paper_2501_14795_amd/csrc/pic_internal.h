@@ -17,7 +17,7 @@ enum : int { kScanLocal = 0, kScanSums = 1, kScanBases = 2 };
 
 struct SortSpecies {
     Parts p;              // the particle arrays (tile-relative cells)
-    int32_t *gcell;       // the caller's cell array: whole-grid cells, written by the publish
+    int32_t *gcell;       // the caller's cell array: whole-grid cells, written by k_settle
     const LeaverRec *lrec;   // leaver particle data written by the push kernel
     Parts stg;            // the motion-class sort's staging, [n]: every particle at its new slot
     LeaverRec *srec;      // the in-place sort's mover staging, [n]: tile t's movers at off[t] + k, in hole order
